@@ -64,8 +64,9 @@ enum {
  * there, and the WIDE codes select it at Nc = 4 too (for comparisons with
  * the register path).  Its update keeps three or, at large Nc, two Nc^2
  * complex matrices in LDS (32 KiB at Nc = 32 in FP64), plus a ring of
- * heatbath draws when two wavefronts share it.  Of a launch shape only the
- * block size applies to it: 64 runs each link's update on one wavefront,
+ * heatbath draws when two wavefronts share it.  Up to Nc = 8 one wavefront
+ * updates four links and no launch shape applies.  Above, of a launch shape
+ * only the block size applies: 64 runs each link's update on one wavefront,
  * 128 on two (the link loads and the vector-unit products shared, the
  * subgroup steps on the first and, where LDS allows, the heatbath draws on
  * the second; the same bits either way; in the FP32 matrix-core form above

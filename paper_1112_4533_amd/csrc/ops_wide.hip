@@ -44,6 +44,10 @@ struct OpsWide {
         return wide_update_threads(nc, f64) > wide::kLanes;
     }
     static void update(const Ctx& c, int kind, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step) {
+        if (c.nc <= kWideSmallMax) {
+            launch_update_small<T>(c, kind == 0 ? 1 : 0, mu, par, beta, k0, k1, step);
+            return;
+        }
         const bool ra = wide_update_regacc(c.nc, f64);
         const bool two = two_waves(c.shape[kind], c.nc);
         if constexpr (!f64) {
@@ -127,6 +131,10 @@ struct OpsWide {
     }
     static void update_batch(const ChainDesc* d, int n, int tiles, int kind, int mu, int par, uint32_t off,
                              const Shape& shape, int nc, hipStream_t s) {
+        if (nc <= kWideSmallMax) {
+            launch_update_small_batch<T>(d, n, tiles, kind == 0 ? 1 : 0, mu, par, off, nc, s);
+            return;
+        }
         const bool ra = wide_update_regacc(nc, f64);
         const bool two = two_waves(shape, nc);
         if constexpr (!f64) {

@@ -532,12 +532,12 @@ int upload_table(sun_batch_t b) {
         for (int i = gr.first; i < gr.first + gr.count; ++i) {
             sun::ChainDesc& c = b->host[i];
             for (int k = 0; k < 5; ++k) c.tile0[k] = t[k];
-            if (gr.wide) {  // one workgroup per updated link, per site, per link
-                t[sun::TILE_HALF_HB] += c.g.Vh;
+            if (gr.wide) {  // one workgroup per updated link (or few of them), per site, per link
+                t[sun::TILE_HALF_HB] += sun::wide_update_tiles(gr.nc, c.g.Vh);
                 t[sun::TILE_SITE] += c.g.V;
                 t[sun::TILE_LINK] += 4 * c.g.V;
                 t[sun::TILE_SPATIAL] += c.g.V / c.g.L[3];
-                t[sun::TILE_HALF_OR] += c.g.Vh;
+                t[sun::TILE_HALF_OR] += sun::wide_update_tiles(gr.nc, c.g.Vh);
                 continue;
             }
             t[sun::TILE_HALF_HB] += sun::half_blocks(c.g, b->shape[SUN_HEATBATH].block);

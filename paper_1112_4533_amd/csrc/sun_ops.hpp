@@ -177,6 +177,18 @@ inline bool wide_handoff(int nc, int f64, size_t ring_bytes) {
     return f64 || wide_update_lds(nc, f64) + ring_bytes <= (size_t)kLdsPerCu / 8;
 }
 
+// Up to Nc = kWideSmallMax an update workgroup (one wavefront) takes
+// kWideSmallLinks links, above it takes one.
+constexpr int kWideSmallMax = 8, kWideSmallLinks = 4;
+inline int wide_update_tiles(int nc, int Vh) {
+    return nc <= kWideSmallMax ? (Vh + kWideSmallLinks - 1) / kWideSmallLinks : Vh;
+}
+template <typename T>
+void launch_update_small(const Ctx& c, int hb, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step);
+template <typename T>
+void launch_update_small_batch(const ChainDesc* d, int n, int tiles, int hb, int mu, int par, uint32_t off, int nc,
+                               hipStream_t s);
+
 void launch_finalize_max2(const double* partial, int nblk, double* out, hipStream_t s);
 void launch_finalize_sum2(const double* partial, int nblk, double* out, double scale, hipStream_t s);
 void launch_plaquette_final(const double* partial, int nblk, double* out, double norm_sp, double norm_tm,

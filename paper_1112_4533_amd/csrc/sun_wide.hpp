@@ -807,6 +807,106 @@ __device__ __forceinline__ int sample_su2_slot(T alpha, const DrawBatch<T>& b, i
     return ho;
 }
 
+// ---------------------------------------------------------------------------
+// Draws by place: sixteen lanes run one subgroup step, and the terms of its
+// draw that do not depend on alpha wait in LDS -- the Kennedy-Pendleton log
+// term and r3^2 of its first four attempts, and its direction -- so that
+// every lane of the place tries all four with two multiplications and a
+// comparison each and none of them has to be moved between lanes.  A step
+// whose first four attempts all reject, or whose alpha is in the Creutz
+// range, draws from the beginning, sixteen attempts at a time.  Either way
+// the lowest accepting attempt of the counter stream wins, as in the
+// sequential sampler, and the accepted attempt's arithmetic is its own.
+// ---------------------------------------------------------------------------
+constexpr int kPlaceLanes = 16;
+constexpr int kQuickHits = 4;  // attempts a record holds
+template <typename T>
+struct alignas(16) DrawRec {
+    T kp[kQuickHits], r3sq[kQuickHits];
+    T cos_t, sin_t, cos_p, sin_p;
+};
+
+// The records of subgroups sg0 .. sg0 + nsteps - 1, by the sixteen lanes of
+// a place: four steps' attempts at a time, then sixteen steps' directions.
+template <typename T>
+__device__ __forceinline__ void fill_draws(DrawRec<T>* rec, int nsteps, uint32_t sg0, uint32_t k0, uint32_t k1,
+                                           uint32_t site, uint32_t step, uint32_t mu_hi) {
+    const int q = (int)threadIdx.x % kPlaceLanes;
+    for (int t0 = 0; t0 < nsteps; t0 += kPlaceLanes / kQuickHits) {
+        const int t = t0 + q / kQuickHits, hit = q % kQuickHits;
+        if (t < nsteps) {
+            const U4 a = philox(site, step, mu_hi | (sg0 + (uint32_t)t), (RNG_ATTEMPT << 24) | (uint32_t)hit, k0, k1);
+            const T r0 = uniform<T>(a.w[0]), r1 = uniform<T>(a.w[1]), r2 = uniform<T>(a.w[2]);
+            const T r3 = uniform<T>(a.w[3]);
+            const T c = draw_cos(Const<T>::two_pi * r1);
+            rec[t].kp[hit] = -(draw_log(r0) + c * c * draw_log(r2));
+            rec[t].r3sq[hit] = r3 * r3;
+        }
+    }
+    for (int t = q; t < nsteps; t += kPlaceLanes) {
+        const U4 d = philox(site, step, mu_hi | (sg0 + (uint32_t)t), RNG_DIRECTION << 24, k0, k1);
+        const T ct = T(1) - T(2) * uniform<T>(d.w[0]);
+        const T phi = Const<T>::two_pi * uniform<T>(d.w[1]);
+        rec[t].cos_t = ct;
+        rec[t].sin_t = d_sqrt(T(1) - ct * ct);
+        rec[t].cos_p = draw_cos(phi);
+        rec[t].sin_p = draw_sin(phi);
+    }
+}
+
+// The draw of the lane's place: alpha and live (a step is there) are the
+// same on its sixteen lanes.  Returns the number of the accepted attempt
+// (1-based), or 0 (skip the step) when all kMaxAttempts were rejected.
+template <typename T>
+__device__ __forceinline__ int place_draw(T alpha, bool live, const DrawRec<T>& rec, uint32_t k0, uint32_t k1,
+                                          uint32_t site, uint32_t step, uint32_t mu_sg, Quat<T>& x) {
+    const bool creutz = alpha < Const<T>::switch_alpha;
+    const T ia = chain_inverse(alpha);
+    T x0 = T(1), rad = T(0);
+    int hit = 0;
+    {
+        const T half = T(0.5) * ia;
+        T l2 = T(0), rh = T(1);
+#pragma unroll
+        for (int a = kQuickHits - 1; a >= 0; --a) {
+            const T lam2 = rec.kp[a] * half;
+            const T rhs = T(1) - lam2;
+            if (rec.r3sq[a] <= rhs) {
+                l2 = lam2;
+                rh = rhs;
+                hit = a + 1;
+            }
+        }
+        x0 = T(1) - T(2) * l2;
+        rad = T(2) * fast_sqrt(l2) * fast_sqrt(rh);
+    }
+    if (__any(live && (creutz || hit == 0))) {
+        if (creutz) hit = 0;
+        const T em = creutz ? d_expm1(T(-2) * alpha) : T(0);
+        const int first_lane = (int)threadIdx.x & (kLanes - kPlaceLanes);
+        for (int h0 = 0; h0 < kMaxAttempts && __any(live && hit == 0); h0 += kPlaceLanes) {
+            const uint32_t mine = (uint32_t)h0 + threadIdx.x % kPlaceLanes;
+            const U4 r = philox(site, step, mu_sg, (RNG_ATTEMPT << 24) | mine, k0, k1);
+            T ax0 = T(1), arad = T(0);
+            const bool ok = su2_attempt(alpha, ia, creutz, em, r, ax0, arad);
+            const uint32_t m = (uint32_t)(__ballot(ok) >> first_lane) & 0xFFFFu;
+            const int a = m ? __ffs(m) - 1 : 0;
+            ax0 = __shfl(ax0, first_lane + a, kLanes);
+            arad = __shfl(arad, first_lane + a, kLanes);
+            if (hit == 0 && m != 0) {
+                x0 = ax0;
+                rad = arad;
+                hit = h0 + a + 1;
+            }
+        }
+    }
+    x.q[0] = x0;
+    x.q[1] = rad * rec.sin_t * rec.cos_p;
+    x.q[2] = rad * rec.sin_t * rec.sin_p;
+    x.q[3] = rad * rec.cos_t;
+    return hit;
+}
+
 // Rows i, j of M (LDS), column c, left-multiplied by the 2x2 form of a,
 // given their current entries x = M_ic and y = M_jc.
 template <typename T>

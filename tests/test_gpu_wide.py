@@ -358,3 +358,22 @@ def test_wide_permutation_links_need_pivoting(gpu, nc, dtype):
     O.reunitarize(U, nc, L)
     assert np.abs(to_np(lat.export()) - U).max() < 1e-13
     assert to_np(lat.unitarity()).max() < 1e-13
+
+
+@pytest.mark.parametrize("L", [(6, 2, 1, 1), (2, 2, 2, 2), (6, 2, 4, 2)])   # 6, 8 and 48 links per phase
+@pytest.mark.parametrize("nc,dtype", [(4, "f32w"), (4, "f64w"), (5, "f32"), (5, "f64"), (6, "f32"), (6, "f64"),
+                                      (7, "f32"), (7, "f64"), (8, "f32"), (8, "f64")])
+def test_wide_four_links_per_wavefront(gpu, nc, dtype, L):
+    """Up to Nc = 8 a wavefront updates four links: every Nc of that form,
+    with a last wavefront that is not full, and with a coupling so small that
+    the draws take the Creutz range and attempts past a record's four."""
+    base = O.new_field(nc, L, hot=True, seed=51)
+    lat = gpu_lattice(gpu, nc, L, dtype, field=base)
+    for kind, mu, par, beta in [(0, 0, 1, beta_for(nc)), (0, 1, 0, 0.3 * nc), (1, 1, 1, 1.0), (1, 0, 0, 1.0)]:
+        before = to_np(lat.export())
+        lat.phase(kind, mu, par, beta, seed=13, step=4)
+        got = to_np(lat.export())
+        sp = twin_spread(before, nc, L, kind, mu, par, beta, 13, 4, rel=REL[dtype[:3]])
+        want = before.copy()
+        m, k = oracle_phase_diag(want, nc, L, kind, mu, par, beta, 13, 4)
+        compare_links(got, want, dtype, m, k, f"nc={nc} {dtype} kind={kind} beta={beta}", spread=sp)
