@@ -1,0 +1,59 @@
+// ops_wide_large.hip -- launchers of the two-wavefront update (Nc >= 9), one
+// workgroup per link; Nc is a run-time argument, the LDS size follows it.
+#include "sun_ops.hpp"
+#include "sun_wide_large.hpp"
+
+namespace sun {
+namespace {
+
+template <typename T, int RANGE, bool HB>
+void launch(const Ctx& c, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step) {
+    wide::k_update_large<T, RANGE, HB><<<wide_update_tiles(c.nc, c.g.Vh), wide::kLargeThreads,
+                                         wide::large_lds<T>(c.nc, HB), c.stream>>>((T2<T>*)c.links, c.g, c.nc, mu, par,
+                                                                                   (T)beta, k0, k1, step);
+}
+template <typename T, int RANGE, bool HB>
+void launch_batch(const ChainDesc* d, int n, int tiles, int mu, int par, uint32_t off, int nc, hipStream_t s) {
+    wide::k_update_large_batch<T, RANGE, HB><<<tiles, wide::kLargeThreads, wide::large_lds<T>(nc, HB), s>>>(
+        d, n, nc, mu, par, off);
+}
+
+// f(range, kind) with both as compile-time constants
+template <typename F>
+void with_range(int nc, int hb, F f) {
+    auto kind = [&](auto range) {
+        if (hb)
+            f(range, std::true_type{});
+        else
+            f(range, std::false_type{});
+    };
+    if (nc <= wide::kLargeMax[0])
+        kind(std::integral_constant<int, 0>{});
+    else if (nc <= wide::kLargeMax[1])
+        kind(std::integral_constant<int, 1>{});
+    else
+        kind(std::integral_constant<int, 2>{});
+}
+
+}  // namespace
+
+template <typename T>
+void launch_update_large(const Ctx& c, int hb, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step) {
+    with_range(c.nc, hb, [&](auto range, auto kind) {
+        launch<T, decltype(range)::value, decltype(kind)::value>(c, mu, par, beta, k0, k1, step);
+    });
+}
+template <typename T>
+void launch_update_large_batch(const ChainDesc* d, int n, int tiles, int hb, int mu, int par, uint32_t off, int nc,
+                               hipStream_t s) {
+    with_range(nc, hb, [&](auto range, auto kind) {
+        launch_batch<T, decltype(range)::value, decltype(kind)::value>(d, n, tiles, mu, par, off, nc, s);
+    });
+}
+
+template void launch_update_large<float>(const Ctx&, int, int, int, double, uint32_t, uint32_t, uint32_t);
+template void launch_update_large<double>(const Ctx&, int, int, int, double, uint32_t, uint32_t, uint32_t);
+template void launch_update_large_batch<float>(const ChainDesc*, int, int, int, int, int, uint32_t, int, hipStream_t);
+template void launch_update_large_batch<double>(const ChainDesc*, int, int, int, int, int, uint32_t, int, hipStream_t);
+
+}  // namespace sun

@@ -61,12 +61,8 @@ inline int check_lattice(int nc, const int L[4], int dtype) {
     if (nc < 2 || nc > SUN_NC_MAX) return fail(SUN_EINVAL, "Nc = %d outside 2..%d", nc, SUN_NC_MAX);
     if (dtype < SUN_F32 || dtype > SUN_F64_WIDE) return fail(SUN_EINVAL, "dtype %d is not a SUN_F* code", dtype);
     if (is_two_row(dtype) && nc != 3) return fail(SUN_EUNSUP, "two-row storage exists for SU(3) only (Nc = %d)", nc);
-    if (is_wide(nc, dtype)) {
-        if (nc < 4) return fail(SUN_EUNSUP, "the workgroup-per-link path starts at Nc = 4 (Nc = %d)", nc);
-        if (sun::wide_update_lds(nc, is_f64(dtype)) > sun::kWideLdsMax)
-            return fail(SUN_EUNSUP, "Nc = %d in FP64 needs %zu bytes of LDS per workgroup (limit %zu)", nc,
-                        sun::wide_update_lds(nc, 1), sun::kWideLdsMax);
-    }
+    if (is_wide(nc, dtype) && nc < 4)
+        return fail(SUN_EUNSUP, "the workgroup-per-link path starts at Nc = 4 (Nc = %d)", nc);
     if (L[0] < 2 || (L[0] & 1)) return fail(SUN_EINVAL, "L[0] = %d must be even and >= 2", L[0]);
     long long V = 1;
     for (int mu = 0; mu < 4; ++mu) {

@@ -143,42 +143,8 @@ const Ops* ops_nc4(int f64);
 const Ops* ops_nc3_two_row(int f64);  // SU(3), rows 0 and 1 stored
 const Ops* ops_wide(int f64);         // 4 <= Nc <= 32: one workgroup per link, link-major storage
 
-// Dynamic LDS of the wide phase kernel, and whether it fits a workgroup.  The
-// kernel keeps three Nc x Nc matrices in LDS, or two with the staple sum in
-// registers; the latter where three would leave fewer than 8 workgroups per
-// CU (FP32 from Nc = 30, FP64 from Nc = 21), since a phase at 8^4 is 2048
-// workgroups and fewer than 8 per CU take it two or more rounds.
-constexpr size_t kWideLdsMax = 64 * 1024;
-inline bool wide_update_regacc(int nc, int f64) { return (size_t)3 * nc * nc * (f64 ? 16 : 8) > kLdsPerCu / 8; }
-// Threads of a large-Nc update workgroup: two wavefronts (the loads and
-// vector-unit products shared, the subgroup steps on the first, and the
-// heatbath draws on the second where wide_handoff allows) where that
-// measured faster on 8^4
-// -- FP32 from Nc = 9 (5-9% per iteration up to Nc = 20; above, where the
-// matrix-core products stay on the first wavefront and only the loads are
-// shared, 2% -- the overrelaxation 6%; below Nc = 9 the second wavefront
-// costs more than it saves), and FP64 where a phase takes two rounds anyway
-// (two matrices of more than 10 KB, Nc >= 26; SU(32) 25.3 -> 20.8 ms) --
-// one otherwise.
-inline int wide_update_threads(int nc, int f64) {
-    if (!f64) return nc >= 9 ? 128 : 64;
-    return (size_t)2 * nc * nc * 16 > kLdsPerCu / 8 ? 128 : 64;
-}
-inline size_t wide_update_lds(int nc, int f64) {
-    return (size_t)(wide_update_regacc(nc, f64) ? 2 : 3) * nc * nc * (f64 ? 16 : 8);
-}
-// Whether the second of two wavefronts draws the heatbath batches for the
-// first (through a ring of ring_bytes in LDS): always in FP64, whose draws
-// (FP64 logarithms and cosines) are costly; in FP32 where the ring still
-// leaves the 8 workgroups per CU a phase at 8^4 needs for one round (the
-// chain gains 2-4% from Nc = 9 to 24 and at 32; at Nc = 28 the ring would
-// cost the second round: 5.6 -> 7.8 ms).
-inline bool wide_handoff(int nc, int f64, size_t ring_bytes) {
-    return f64 || wide_update_lds(nc, f64) + ring_bytes <= (size_t)kLdsPerCu / 8;
-}
-
 // Up to Nc = kWideSmallMax an update workgroup (one wavefront) takes
-// kWideSmallLinks links, above it takes one.
+// kWideSmallLinks links, above it (two wavefronts) one.
 constexpr int kWideSmallMax = 8, kWideSmallLinks = 4;
 inline int wide_update_tiles(int nc, int Vh) {
     return nc <= kWideSmallMax ? (Vh + kWideSmallLinks - 1) / kWideSmallLinks : Vh;
@@ -187,6 +153,11 @@ template <typename T>
 void launch_update_small(const Ctx& c, int hb, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step);
 template <typename T>
 void launch_update_small_batch(const ChainDesc* d, int n, int tiles, int hb, int mu, int par, uint32_t off, int nc,
+                               hipStream_t s);
+template <typename T>
+void launch_update_large(const Ctx& c, int hb, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step);
+template <typename T>
+void launch_update_large_batch(const ChainDesc* d, int n, int tiles, int hb, int mu, int par, uint32_t off, int nc,
                                hipStream_t s);
 
 void launch_finalize_max2(const double* partial, int nblk, double* out, hipStream_t s);

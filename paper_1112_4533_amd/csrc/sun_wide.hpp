@@ -1,24 +1,20 @@
-// sun_wide.hpp -- SU(Nc) for large Nc (4 <= Nc <= 32): one 64-lane
-// workgroup per link (paper Sec. 3, generic SU(Nc) code; Sec. 4, the
-// large-Nc runs at 8^4).
+// sun_wide.hpp -- SU(Nc) for large Nc (4 <= Nc <= 32), one workgroup per link
+// (paper Sec. 3, generic SU(Nc) code; Sec. 4, the large-Nc runs at 8^4): the
+// SU(2) draw of the subgroup steps, re-unitarization, observables, start
+// configuration and field transfer.  The phase update is in
+// sun_wide_small.hpp (Nc <= 8) and sun_wide_large.hpp.
 //
 // At large Nc a link no longer fits in one work-item's registers (Nc = 32 is
-// 2048 reals), so a workgroup of one wavefront (or two) owns one link: the
-// matrices of the update live in LDS, every product is spread over the lanes
-// element by element, and the SU(2) subgroup steps (Nc(Nc-1)/2 of them)
-// update two rows with one lane per column, several steps at a time.  Links are stored
-// link-major (the Nc^2 complex entries of one link are contiguous), so the
-// workgroup reads a link with unit stride.  Operands that enter a product
-// daggered are transposed while they are copied into LDS, so that every
-// product reads one operand by broadcast and the other with unit stride.
+// 2048 reals): its matrices live in LDS, spread over the lanes.  Links are
+// stored link-major (the Nc^2 complex entries of one link are contiguous), so
+// a workgroup reads a link with unit stride.
 //
 // The arithmetic is that of the register kernels: the same closing staple,
 // W = U A, the lexicographic subgroup order (run several steps at a time
 // where they share no index, which gives the same bits: sun_pairs.hpp), the
-// quaternion projection, the same Philox counters, and an SU(2) draw whose
-// 64 attempts are evaluated one per lane, the first accepted one winning
-// (which is the sequential draw's result).  Reductions and re-unitarization
-// are FP64.
+// quaternion projection, the same Philox counters, and an SU(2) draw that
+// takes the lowest accepting attempt, the sequential draw's result.
+// Reductions and re-unitarization are FP64.
 #pragma once
 
 #include <cfloat>
@@ -33,13 +29,6 @@ constexpr int kLanes = 64;
 static_assert(kMaxAttempts == kLanes, "one SU(2) attempt per lane");
 constexpr int kNcMin = 4, kNcMax = 32;
 
-// Buffers (n x n complex) the phase kernel keeps in LDS.
-constexpr int kUpdateBuffers = 4;
-
-template <typename T>
-__host__ __device__ inline size_t update_lds(int n) {
-    return (size_t)kUpdateBuffers * n * n * sizeof(T2<T>);
-}
 __host__ __device__ inline size_t fp64_lds(int n, int buffers) { return (size_t)buffers * n * n * sizeof(double2); }
 
 template <typename T>
@@ -56,44 +45,34 @@ __device__ __forceinline__ const T2<T>* link_at(const T2<T>* U, int n2, int mu, 
     return U + ((size_t)(mu * 2 + par) * Vh + h) * n2;
 }
 
-// dst (LDS, type D) = src or src^dag (global, type S), converted.  Each
+// dst (LDS, type D) = src (global, type S), converted.  Each
 // lane issues the global loads of kLoadBatch entries before it stores any,
 // so a link costs a few load latencies instead of one per entry.
 constexpr int kLoadBatch = 8;
 
-template <typename D, typename S, int NT = kLanes>
-__device__ __forceinline__ void lds_load(T2<D>* dst, const T2<S>* src, int n, bool dag) {
+template <typename D, typename S>
+__device__ __forceinline__ void lds_load(T2<D>* dst, const T2<S>* src, int n) {
     const int n2 = n * n;
-    if (n2 <= NT) {  // one entry per lane
+    if (n2 <= kLanes) {  // one entry per lane
         const int e = threadIdx.x;
         if (e < n2) {
             const T2<S> v = src[e];
-            if (dag) {
-                const int i = e / n, j = e - i * n;
-                dst[j * n + i] = cpx<D>((D)v.x, -(D)v.y);
-            } else {
-                dst[e] = cpx<D>((D)v.x, (D)v.y);
-            }
+            dst[e] = cpx<D>((D)v.x, (D)v.y);
         }
         return;
     }
-    for (int e0 = threadIdx.x; e0 < n2; e0 += kLoadBatch * NT) {
+    for (int e0 = threadIdx.x; e0 < n2; e0 += kLoadBatch * kLanes) {
         T2<S> v[kLoadBatch];
 #pragma unroll
         for (int c = 0; c < kLoadBatch; ++c) {
-            const int e = e0 + c * NT;
+            const int e = e0 + c * kLanes;
             if (e < n2) v[c] = src[e];
         }
 #pragma unroll
         for (int c = 0; c < kLoadBatch; ++c) {
-            const int e = e0 + c * NT;
+            const int e = e0 + c * kLanes;
             if (e >= n2) break;
-            if (dag) {
-                const int i = e / n, j = e - i * n;
-                dst[j * n + i] = cpx<D>((D)v[c].x, -(D)v[c].y);
-            } else {
-                dst[e] = cpx<D>((D)v[c].x, (D)v[c].y);
-            }
+            dst[e] = cpx<D>((D)v[c].x, (D)v[c].y);
         }
     }
 }
@@ -157,223 +136,21 @@ __device__ __forceinline__ void lds_mm_rows(T2<T>* C, const T2<T>* A, const T2<T
     }
 }
 
-// The same product on the matrix cores for FP32 and kMfmaMinN < n <= 32:
-// the complex product is four real 32 x 32 x 32 products (C_re += A_re B_re
-// - A_im B_im, C_im += A_re B_im + A_im B_re), each 16 v_mfma_f32_32x32x2f32
-// over k in pairs, with rows, columns and k beyond n read as zero.  Operand
-// layout: lane l gives A[l mod 32][k0 + l / 32] and B[k0 + l / 32][l mod 32];
-// result register r of lane l is entry (8 (r / 4) + 4 (l / 32) + r mod 4,
-// l mod 32).  Every lane takes part (the matrix instructions need the whole
-// wavefront), and all reads of A and B precede the stores, so C may be A
-// when acc is false.  Below kMfmaMinN the padded tile wastes more than the
-// VALU product costs.
-constexpr int kMfmaMinN = 20;
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ void lds_mm_mfma(T2<float>* C, const T2<float>* A, const T2<float>* B, int n, bool acc) {
-    const int l = threadIdx.x;
-    const int lo = l & 31, hi = l >> 5;
-    f32x16 cr, ci;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = 8 * (r / 4) + 4 * hi + (r % 4);
-        T2<float> c = cpx<float>(0.f, 0.f);
-        if (acc && i < n && lo < n) c = C[i * n + lo];
-        cr[r] = c.x;
-        ci[r] = c.y;
-    }
-    // the real and imaginary accumulations alternate, so that consecutive
-    // matrix instructions do not wait on each other's result
-#pragma unroll 2
-    for (int k0 = 0; k0 < n; k0 += 2) {
-        const int k = k0 + hi;
-        T2<float> a = cpx<float>(0.f, 0.f), b = cpx<float>(0.f, 0.f);
-        if (k < n && lo < n) {
-            a = A[lo * n + k];
-            b = B[k * n + lo];
-        }
-        cr = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, cr, 0, 0, 0);
-        ci = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.y, ci, 0, 0, 0);
-        cr = __builtin_amdgcn_mfma_f32_32x32x2f32(-a.y, b.y, cr, 0, 0, 0);
-        ci = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.x, ci, 0, 0, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = 8 * (r / 4) + 4 * hi + (r % 4);
-        if (i < n && lo < n) C[i * n + lo] = cpx<float>(cr[r], ci[r]);
-    }
-}
-
-// Row groups of the vector-unit products on NT threads (NT / 64
-// wavefronts): each wavefront holds 64 / n groups of n lanes, group i0 =
-// (wavefront) * (64 / n) + lane / n taking column j = lane mod n and rows
-// i0, i0 + g, ... (g groups in all).  A group never spans two wavefronts,
-// and every entry is computed by one lane with the same operations in the
-// same order whatever NT is, so the products give the same bits with one
-// wavefront or two.
-template <int NT>
-struct RowMap {
-    int g, j, i0, cnt, most;
-    bool active;
-    __device__ __forceinline__ explicit RowMap(int n) {
-        const int gw = kLanes / n;
-        const int w = (int)threadIdx.x / kLanes, l = (int)threadIdx.x % kLanes;
-        g = gw * (NT / kLanes);
-        active = l < gw * n;
-        j = l % n;
-        i0 = w * gw + l / n;
-        cnt = (n - i0 + g - 1) / g;  // rows i0 + g t < n of this lane
-        most = (n + g - 1) / g;      // rows of group 0, the most of any group
-    }
-};
-
-// MM: the matrix-core form (FP32, kMfmaMinN < n), compiled into its own
-// kernel variant so that the others keep their register budget.
-// RMAX caps the rows a lane takes at a time (fewer registers).
-template <typename T, bool MM = false, int RMAX = 4, int NT = kLanes>
+// The product by one wavefront: 64 / n groups of n lanes, group i0 = lane / n
+// taking column j = lane mod n and rows i0, i0 + g, ... (g groups in all).
+template <typename T>
 __device__ __forceinline__ void lds_mm(T2<T>* C, const T2<T>* A, const T2<T>* B, int n, bool acc) {
-    if constexpr (MM) {
-        static_assert(sizeof(T) == 4, "the matrix-core product is FP32");
-        if (threadIdx.x < kLanes) lds_mm_mfma(C, A, B, n, acc);  // the whole tile on the first wavefront
-        return;
-    }
-    const RowMap<NT> m(n);
-    if (!m.active) return;
-    if (RMAX >= 4 && m.most >= 4)
-        lds_mm_rows<T, 4>(C, A, B, n, acc, m.g, m.j, m.i0, m.cnt);
-    else if (m.most >= 2)
-        lds_mm_rows<T, 2>(C, A, B, n, acc, m.g, m.j, m.i0, m.cnt);
+    const int g = kLanes / n, l = (int)threadIdx.x;
+    if (l >= g * n) return;
+    const int j = l % n, i0 = l / n;
+    const int cnt = (n - i0 + g - 1) / g;  // rows i0 + g t < n of this lane
+    const int most = (n + g - 1) / g;      // rows of group 0, the most of any group
+    if (most >= 4)
+        lds_mm_rows<T, 4>(C, A, B, n, acc, g, j, i0, cnt);
+    else if (most >= 2)
+        lds_mm_rows<T, 2>(C, A, B, n, acc, g, j, i0, cnt);
     else
-        lds_mm_rows<T, 1>(C, A, B, n, acc, m.g, m.j, m.i0, m.cnt);
-}
-
-// ---------------------------------------------------------------------------
-// A product accumulator in registers instead of LDS (the staple sum, and W =
-// U A on its way into LDS), so that the update kernel holds two matrices in
-// LDS instead of three where LDS limits the workgroups per CU.  Each lane
-// keeps the entries it owns in the LDS products above: on the vector units
-// column j = lane mod n, rows i0 + g t (at most kAccRows of them); on the
-// matrix cores the 16 result registers of its 32 x 32 tile.  The products
-// are the same operations in the same order as lds_mm with C in LDS, so the
-// results are the same bits.
-// ---------------------------------------------------------------------------
-constexpr int kAccRows = 16;   // rows of the most loaded lane: ceil(n / (64 / n)) <= 16 for n <= 32
-
-// NT threads: at most kAccRows * 64 / NT rows per lane.
-template <typename T, bool MM, int NT = kLanes>
-struct Acc {
-    static constexpr int kRows = kAccRows * kLanes / NT;
-    T2<T> e[kRows];
-    __device__ __forceinline__ void zero() {
-#pragma unroll
-        for (int t = 0; t < kRows; ++t) e[t] = cpx<T>(T(0), T(0));
-    }
-};
-template <int NT>
-struct Acc<float, true, NT> {
-    f32x16 re, im;
-    __device__ __forceinline__ void zero() {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) re[r] = im[r] = 0.f;
-    }
-};
-
-// c += A B (A, B in LDS) on the vector units, R rows of the lane at a time.
-template <typename T, int R, int NT>
-__device__ __forceinline__ void acc_mm_rows(Acc<T, false, NT>& c, const T2<T>* A, const T2<T>* B, int n, int g,
-                                            int j, int i0, int cnt, int most) {
-#pragma unroll
-    for (int t0 = 0; t0 < Acc<T, false, NT>::kRows; t0 += R) {
-        if (t0 >= most) break;  // the same for every lane
-        int row[R];
-        T r[R], m[R];
-#pragma unroll
-        for (int t = 0; t < R; ++t) {
-            const int tt = t0 + t < cnt ? t0 + t : cnt - 1;
-            row[t] = (i0 + g * tt) * n;
-            r[t] = c.e[t0 + t].x;
-            m[t] = c.e[t0 + t].y;
-        }
-        int k = 0;
-        for (; k + 4 <= n; k += 4) {
-            T2<T> y[4], x[4][R];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                y[q] = B[(k + q) * n + j];
-#pragma unroll
-                for (int t = 0; t < R; ++t) x[q][t] = A[row[t] + k + q];
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int t = 0; t < R; ++t) cmac(r[t], m[t], x[q][t].x, x[q][t].y, y[q].x, y[q].y);
-        }
-        for (; k < n; ++k) {
-            const T2<T> y = B[k * n + j];
-#pragma unroll
-            for (int t = 0; t < R; ++t) {
-                const T2<T> x = A[row[t] + k];
-                cmac(r[t], m[t], x.x, x.y, y.x, y.y);
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < R; ++t)
-            if (t0 + t < cnt) c.e[t0 + t] = cpx<T>(r[t], m[t]);
-    }
-}
-
-template <typename T, bool MM, int NT>
-__device__ __forceinline__ void acc_mm(Acc<T, MM, NT>& c, const T2<T>* A, const T2<T>* B, int n) {
-    if constexpr (MM) {
-        const int l = threadIdx.x;
-        if (l >= kLanes) return;  // the whole tile on the first wavefront
-        const int lo = l & 31, hi = l >> 5;
-#pragma unroll 2
-        for (int k0 = 0; k0 < n; k0 += 2) {
-            const int k = k0 + hi;
-            T2<float> a = cpx<float>(0.f, 0.f), b = cpx<float>(0.f, 0.f);
-            if (k < n && lo < n) {
-                a = A[lo * n + k];
-                b = B[k * n + lo];
-            }
-            c.re = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, c.re, 0, 0, 0);
-            c.im = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.y, c.im, 0, 0, 0);
-            c.re = __builtin_amdgcn_mfma_f32_32x32x2f32(-a.y, b.y, c.re, 0, 0, 0);
-            c.im = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.x, c.im, 0, 0, 0);
-        }
-    } else {
-        const RowMap<NT> m(n);
-        if (!m.active) return;
-        // FP64 takes two rows at a time: with four, the kernel's registers
-        // (the sum itself is 64 VGPRs at Nc = 32) left one wave per SIMD
-        if (sizeof(T) == 4 && m.most >= 4)
-            acc_mm_rows<T, 4, NT>(c, A, B, n, m.g, m.j, m.i0, m.cnt, m.most);
-        else if (m.most >= 2)
-            acc_mm_rows<T, 2, NT>(c, A, B, n, m.g, m.j, m.i0, m.cnt, m.most);
-        else
-            acc_mm_rows<T, 1, NT>(c, A, B, n, m.g, m.j, m.i0, m.cnt, m.most);
-    }
-}
-
-// C (LDS) = the accumulator.
-template <typename T, bool MM, int NT>
-__device__ __forceinline__ void acc_store(T2<T>* C, const Acc<T, MM, NT>& c, int n) {
-    if constexpr (MM) {
-        const int l = threadIdx.x;
-        if (l >= kLanes) return;
-        const int lo = l & 31, hi = l >> 5;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = 8 * (r / 4) + 4 * hi + (r % 4);
-            if (i < n && lo < n) C[i * n + lo] = cpx<float>(c.re[r], c.im[r]);
-        }
-    } else {
-        const RowMap<NT> m(n);
-        if (!m.active) return;
-#pragma unroll
-        for (int t = 0; t < Acc<T, MM, NT>::kRows; ++t)
-            if (t < m.cnt) C[(m.i0 + m.g * t) * n + m.j] = c.e[t];
-    }
+        lds_mm_rows<T, 1>(C, A, B, n, acc, g, j, i0, cnt);
 }
 
 // Cross-lane moves of a wavefront without the LDS: lane l receives the
@@ -494,363 +271,59 @@ __device__ __forceinline__ T chain_unit_quat(const Quat<T>& p, Quat<T>& v) {
     return unit_quat(p, v);
 }
 
-// SU(2) draws of the subgroup steps, eight subgroups per pair of Philox
-// passes.  The hybrid sampler accepts an attempt with probability at least
-// about 0.71, so the first few attempts almost always decide: lane l holds
-// the words of attempt l mod 8 of subgroup sg0 + l / 8, and lanes l hold the
-// direction words of subgroup sg0 + l mod 8.  A draw whose first eight
-// attempts all reject (about 5e-5 of draws) runs attempts 8 .. 63 one per
-// lane.  Either way the draw takes the lowest accepting attempt of the
-// counter-based stream, as the sequential sampler does.
-constexpr int kSgBatch = 8;                    // subgroups per batch
-constexpr int kFirstHits = kLanes / kSgBatch;  // attempts per subgroup in a batch
-
-// What a batch keeps per lane: the uniforms of its attempt that the two
-// samplers test (r0, r1, r3) and the Kennedy-Pendleton log term
-// -(log r0 + cos^2(2 pi r1) log r2), which does not depend on alpha; and the
-// direction of subgroup sg0 + lane mod 8 as cos/sin of its polar angle and
-// of its azimuth.  Only the alpha-dependent remainder of a draw is left on
-// the sequential chain of subgroup steps.
-template <typename T>
-struct DrawBatch {
-    T r0, r1, r3, kp;
-    T cos_t, sin_t, cos_p, sin_p;
-};
-
-// Lane l's share of a batch whose lane group l / 8 draws the attempts of
-// subgroup sg_att and whose lanes l mod 8 = g hold the direction of the
-// subgroup of group g, sg_dir.
-template <typename T>
-__device__ __forceinline__ DrawBatch<T> draw_batch_of(uint32_t k0, uint32_t k1, uint32_t site, uint32_t step,
-                                                      uint32_t mu_hi, uint32_t sg_att, uint32_t sg_dir, uint32_t l) {
-    const U4 a = philox(site, step, mu_hi | sg_att, (RNG_ATTEMPT << 24) | (l % kFirstHits), k0, k1);
-    const U4 d = philox(site, step, mu_hi | sg_dir, RNG_DIRECTION << 24, k0, k1);
-    DrawBatch<T> b;
-    b.r0 = uniform<T>(a.w[0]);
-    b.r1 = uniform<T>(a.w[1]);
-    const T r2 = uniform<T>(a.w[2]);
-    b.r3 = uniform<T>(a.w[3]);
-    const T c = draw_cos(Const<T>::two_pi * b.r1);
-    b.kp = -(draw_log(b.r0) + c * c * draw_log(r2));
-    b.cos_t = T(1) - T(2) * uniform<T>(d.w[0]);
-    b.sin_t = d_sqrt(T(1) - b.cos_t * b.cos_t);
-    const T phi = Const<T>::two_pi * uniform<T>(d.w[1]);
-    b.cos_p = draw_cos(phi);
-    b.sin_p = draw_sin(phi);
-    return b;
-}
-// The batch of subgroups sg0 .. sg0 + 7.
-template <typename T>
-__device__ __forceinline__ DrawBatch<T> draw_batch(uint32_t k0, uint32_t k1, uint32_t site, uint32_t step,
-                                                   uint32_t mu_hi, uint32_t sg0, uint32_t l) {
-    return draw_batch_of<T>(k0, k1, site, step, mu_hi, sg0 + l / kFirstHits, sg0 + l % kSgBatch, l);
-}
-
-// ---------------------------------------------------------------------------
-// The subgroup steps in slots of SW (the order of pairs::make_table, which
-// gives the link of the fixed order bit for bit): in each slot the lanes
-// 64 m / SW .. 64 (m + 1) / SW - 1 run place m, each lane owning columns of
-// U and of W.  A batch covers the eight subgroups of 8 / SW slots, lane
-// group g drawing for place g mod SW of slot g / SW; its eight steps are
-// four table words.  Four steps per slot from Nc = 10 (SU(32): 139 slots
-// instead of 257), where the shorter chain pays for four column updates
-// per lane; two below, where it does not (Nc = 5: 7 slots either way).
-// Every width gives the same bits.
-// ---------------------------------------------------------------------------
-constexpr int kSlot4MinN = 10;
-__host__ __device__ constexpr int slot_steps(int n) { return n >= kSlot4MinN ? 4 : 2; }
-template <int SW>
-struct SlotShape {
-    static constexpr int kStepLanes = kLanes / SW;                              // lanes per step
-    static constexpr int kStepCols = (kNcMax + kStepLanes - 1) / kStepLanes;     // columns per lane
-    static constexpr int kWords = SW / 2;                                        // table words per slot
-    static constexpr int kPerBatch = kSgBatch / SW;                              // slots per batch
-};
-constexpr int kBatchWords = kSgBatch / 2;
-static __constant__ pairs::Table<2> kPairTable2 = pairs::make_table<2>();
-static __constant__ pairs::Table<4> kPairTable4 = pairs::make_table<4>();
-constexpr pairs::Table<2> kPairTable2Host = pairs::make_table<2>();
-constexpr pairs::Table<4> kPairTable4Host = pairs::make_table<4>();
-// The table words of a link, 64 to a register across the wavefront (lane l
-// holds word 64 w + l of window w), so that a slot reads its steps with
-// readlane.
-constexpr int max_words() {
-    const int a = pairs::slots(kPairTable2Host, kNcMax), b = 2 * pairs::slots(kPairTable4Host, kNcMax);
-    return a > b ? a : b;
-}
-constexpr int kPairWindows = (max_words() + kLanes - 1) / kLanes;
-static_assert(kLanes % kBatchWords == 0, "a batch's words share a window");
-static_assert(kBatchWords == 4, "draw_pair_batch selects among four words");
-constexpr uint32_t kNoWord = 0xFFFFFFFFu;  // beyond the last slot: no steps
-
-template <int SW>
-__device__ __forceinline__ void pair_windows(int n, uint32_t (&win)[kPairWindows], int& nslot) {
-    const uint16_t* first = SW == 2 ? kPairTable2.first : kPairTable4.first;
-    const uint32_t* word = SW == 2 ? kPairTable2.word : kPairTable4.word;
-    constexpr int kw = SlotShape<SW>::kWords;
-    const int f = first[n] * kw;
-    nslot = first[n + 1] - first[n];
-    const int l = (int)(threadIdx.x & (kLanes - 1));
-#pragma unroll
-    for (int w = 0; w < kPairWindows; ++w) win[w] = kLanes * w + l < nslot * kw ? word[f + kLanes * w + l] : kNoWord;
-}
-// The next window to the front (after every 64 words).
-__device__ __forceinline__ void pair_windows_shift(uint32_t (&win)[kPairWindows]) {
-#pragma unroll
-    for (int w = 0; w + 1 < kPairWindows; ++w) win[w] = win[w + 1];
-    win[kPairWindows - 1] = kNoWord;
-}
-__device__ __forceinline__ uint32_t pair_at(uint32_t win0, int u) {
-    return (uint32_t)__builtin_amdgcn_readlane((int)win0, u);
-}
-// Subgroup number (the Philox counter) of half m of a table word; 0 for an
-// empty place, whose draws go unused.
-__device__ __forceinline__ uint32_t pair_sg(uint32_t e, int m, int n) {
-    const int i = (int)((e >> (16 * m)) & 0xFF), j = (int)((e >> (16 * m + 8)) & 0xFF);
-    return i == pairs::kNone ? 0u : pairs::step_index(n, i, j);
-}
-// The batch of the four table words u0 .. u0 + 3 of window win0.
-template <typename T>
-__device__ __forceinline__ DrawBatch<T> draw_pair_batch(uint32_t k0, uint32_t k1, uint32_t site, uint32_t step,
-                                                        uint32_t mu_hi, uint32_t win0, int u0, int n, uint32_t l) {
-    uint32_t e[kBatchWords];
-#pragma unroll
-    for (int q = 0; q < kBatchWords; ++q) e[q] = pair_at(win0, u0 + q);
-    auto sg_of = [&](uint32_t g) {
-        const uint32_t q = g >> 1;
-        const uint32_t es = q == 0 ? e[0] : q == 1 ? e[1] : q == 2 ? e[2] : e[3];
-        return pair_sg(es, (int)(g & 1), n);
-    };
-    return draw_batch_of<T>(k0, k1, site, step, mu_hi, sg_of(l / kFirstHits), sg_of(l % kSgBatch), l);
-}
-
-// A ring of two batches in LDS (slot, field, lane), through which a second
-// wavefront hands the first the draws of the next eight subgroups.
-constexpr int kBatchFields = 8;
-template <typename T>
-__host__ __device__ inline size_t batch_ring_bytes() {
-    return (size_t)2 * kBatchFields * kLanes * sizeof(T);
-}
-// Dynamic LDS of an update launch beyond its matrices: the ring, where the
-// second of two wavefronts draws the heatbath batches (ho: hand-off on).
-template <typename T>
-__host__ __device__ inline size_t handoff_lds(bool ho) {
-    return ho ? batch_ring_bytes<T>() : 0;
-}
-template <typename T>
-__device__ __forceinline__ void ring_store(T* ring, int slot, int l, const DrawBatch<T>& b) {
-    T* r = ring + (size_t)slot * kBatchFields * kLanes + l;
-    r[0 * kLanes] = b.r0;
-    r[1 * kLanes] = b.r1;
-    r[2 * kLanes] = b.r3;
-    r[3 * kLanes] = b.kp;
-    r[4 * kLanes] = b.cos_t;
-    r[5 * kLanes] = b.sin_t;
-    r[6 * kLanes] = b.cos_p;
-    r[7 * kLanes] = b.sin_p;
-}
-template <typename T>
-__device__ __forceinline__ DrawBatch<T> ring_load(const T* ring, int slot, int l) {
-    const T* r = ring + (size_t)slot * kBatchFields * kLanes + l;
-    DrawBatch<T> b;
-    b.r0 = r[0 * kLanes];
-    b.r1 = r[1 * kLanes];
-    b.r3 = r[2 * kLanes];
-    b.kp = r[3 * kLanes];
-    b.cos_t = r[4 * kLanes];
-    b.sin_t = r[5 * kLanes];
-    b.cos_p = r[6 * kLanes];
-    b.sin_p = r[7 * kLanes];
-    return b;
-}
-
-// One attempt from a batch's precomputed terms: the same tests and results
-// as su2_attempt on the attempt's Philox words.
-template <typename T>
-__device__ __forceinline__ bool su2_attempt_batched(T alpha, T ia, bool creutz, T em, const DrawBatch<T>& b, T& x0,
-                                                    T& rad) {
-    if (creutz) {
-        x0 = (alpha == T(0)) ? T(2) * b.r0 - T(1) : T(1) + d_log1p((T(1) - b.r0) * em) * ia;
-        const T rhs = T(1) - x0 * x0;
-        if (b.r1 * b.r1 <= rhs) {
-            rad = fast_sqrt(rhs);
-            return true;
-        }
-    } else {
-        const T lam2 = b.kp * (T(0.5) * ia);
-        const T rhs = T(1) - lam2;
-        if (b.r3 * b.r3 <= rhs) {
-            x0 = T(1) - T(2) * lam2;
-            rad = T(2) * fast_sqrt(lam2) * fast_sqrt(rhs);
-            return true;
-        }
-    }
-    return false;
-}
-
-// The draw of subgroup mu_sg, slot s of batch b.  Returns the number of the
-// accepted attempt (1-based), or 0 (skip the step) when all kMaxAttempts
-// attempts are rejected.
-template <typename T>
-__device__ __forceinline__ int sample_su2_lanes(T alpha, const DrawBatch<T>& b, int s, uint32_t k0, uint32_t k1,
-                                                uint32_t site, uint32_t step, uint32_t mu_sg, Quat<T>& x) {
-    const bool creutz = alpha < Const<T>::switch_alpha;
-    const T em = creutz ? d_expm1(T(-2) * alpha) : T(0);
-    const T ia = chain_inverse(alpha);
-    T x0 = T(1), rad = T(0);
-    bool ok = su2_attempt_batched(alpha, ia, creutz, em, b, x0, rad);
-    unsigned long long mask = __ballot(ok) & (0xFFull << (kFirstHits * s));
-    int hit0 = -kFirstHits * s;  // attempt number of lane 0, 0-based
-    if (mask == 0ull) {
-        const uint32_t hit = threadIdx.x + kFirstHits;
-        const U4 r = philox(site, step, mu_sg, (RNG_ATTEMPT << 24) | hit, k0, k1);
-        ok = hit < (uint32_t)kMaxAttempts && su2_attempt(alpha, ia, creutz, em, r, x0, rad);
-        mask = __ballot(ok);
-        if (mask == 0ull) return 0;
-        hit0 = kFirstHits;
-    }
-    const int first = __ffsll(mask) - 1;  // the same on every lane
-    x0 = lane_value(x0, first);
-    rad = lane_value(rad, first);
-    const T cos_t = lane_value(b.cos_t, s), sin_t = lane_value(b.sin_t, s);
-    const T cos_p = lane_value(b.cos_p, s), sin_p = lane_value(b.sin_p, s);
-    x.q[0] = x0;
-    x.q[1] = rad * sin_t * cos_p;
-    x.q[2] = rad * sin_t * sin_p;
-    x.q[3] = rad * cos_t;
-    return hit0 + first + 1;
-}
-
-// The draws of the np subgroups of slot q of a batch (lane groups
-// kSlotSteps q + m hold the attempts of place m), as sample_su2_lanes draws
-// each: alpha is the lane's own step's (place lane / (64 / kSlotSteps)),
-// mu_sg the places' counters.  Returns, for the lane's own step, the accepted
-// attempt's number (0: skip the step), and its element in x.
-template <typename T, int kSlotSteps>
-__device__ __forceinline__ int sample_su2_slot(T alpha, const DrawBatch<T>& b, int q, int np, uint32_t k0,
-                                               uint32_t k1, uint32_t site, uint32_t step,
-                                               const uint32_t (&mu_sg)[kSlotSteps], Quat<T>& x) {
-    constexpr int kStepLanes = SlotShape<kSlotSteps>::kStepLanes;
-    const int l = (int)threadIdx.x;
-    T alm[kSlotSteps];
-#pragma unroll
-    for (int m = 0; m < kSlotSteps; ++m) alm[m] = m < np ? lane_value(alpha, m * kStepLanes) : alm[0];
-    // each lane tries its attempt with the alpha of the subgroup it draws for
-    const int gm = (l / kFirstHits) % kSlotSteps;
-    T al = alm[0];
-#pragma unroll
-    for (int m = 1; m < kSlotSteps; ++m)
-        if (gm == m) al = alm[m];
-    const bool creutz = al < Const<T>::switch_alpha;
-    const T em = creutz ? d_expm1(T(-2) * al) : T(0);
-    const T ia = chain_inverse(al);
-    T x0 = T(1), rad = T(0);
-    const bool ok = su2_attempt_batched(al, ia, creutz, em, b, x0, rad);
-    const unsigned long long ball = __ballot(ok);
-    T mx0[kSlotSteps], mrad[kSlotSteps];
-    int hit[kSlotSteps];
-#pragma unroll
-    for (int m = 0; m < kSlotSteps; ++m) {
-        mx0[m] = T(1);
-        mrad[m] = T(0);
-        hit[m] = 0;
-        if (m >= np) continue;
-        const int g = kSlotSteps * q + m;
-        unsigned long long mask = ball & (0xFFull << (kFirstHits * g));
-        int hit0 = -kFirstHits * g;
-        T fx0 = x0, frad = rad;
-        if (mask == 0ull) {  // the first eight attempts all rejected: attempts 8 .. 63, one per lane
-            const T a = alm[m];
-            const bool cr = a < Const<T>::switch_alpha;
-            const T e2 = cr ? d_expm1(T(-2) * a) : T(0);
-            const T i2 = chain_inverse(a);
-            const uint32_t h = (uint32_t)l + kFirstHits;
-            const U4 r = philox(site, step, mu_sg[m], (RNG_ATTEMPT << 24) | h, k0, k1);
-            fx0 = T(1);
-            frad = T(0);
-            const bool ok2 = h < (uint32_t)kMaxAttempts && su2_attempt(a, i2, cr, e2, r, fx0, frad);
-            mask = __ballot(ok2);
-            hit0 = kFirstHits;
-        }
-        if (mask != 0ull) {
-            const int first = __ffsll(mask) - 1;  // the same on every lane
-            mx0[m] = lane_value(fx0, first);
-            mrad[m] = lane_value(frad, first);
-            hit[m] = hit0 + first + 1;
-        }
-    }
-    // the lane's own step; the direction of lane group g sits in the lanes
-    // l mod 8 = g (read at uniform lanes, then selected)
-    const int mo = l / kStepLanes;
-    T x0o = mx0[0], ro = mrad[0];
-    int ho = hit[0];
-    T ct = lane_value(b.cos_t, kSlotSteps * q), st = lane_value(b.sin_t, kSlotSteps * q);
-    T cp = lane_value(b.cos_p, kSlotSteps * q), sp = lane_value(b.sin_p, kSlotSteps * q);
-#pragma unroll
-    for (int m = 1; m < kSlotSteps; ++m) {
-        const T ctm = lane_value(b.cos_t, kSlotSteps * q + m), stm = lane_value(b.sin_t, kSlotSteps * q + m);
-        const T cpm = lane_value(b.cos_p, kSlotSteps * q + m), spm = lane_value(b.sin_p, kSlotSteps * q + m);
-        if (mo == m && m < np) {
-            x0o = mx0[m];
-            ro = mrad[m];
-            ho = hit[m];
-            ct = ctm;
-            st = stm;
-            cp = cpm;
-            sp = spm;
-        }
-    }
-    x.q[0] = x0o;
-    x.q[1] = ro * st * cp;
-    x.q[2] = ro * st * sp;
-    x.q[3] = ro * ct;
-    return ho;
-}
-
 // ---------------------------------------------------------------------------
 // Draws by place: sixteen lanes run one subgroup step, and the terms of its
 // draw that do not depend on alpha wait in LDS -- the Kennedy-Pendleton log
-// term and r3^2 of its first four attempts, and its direction -- so that
-// every lane of the place tries all four with two multiplications and a
+// term and r3^2 of its first three attempts, and its direction -- so that
+// every lane of the place tries all three with two multiplications and a
 // comparison each and none of them has to be moved between lanes.  A step
-// whose first four attempts all reject, or whose alpha is in the Creutz
-// range, draws from the beginning, sixteen attempts at a time.  Either way
-// the lowest accepting attempt of the counter stream wins, as in the
-// sequential sampler, and the accepted attempt's arithmetic is its own.
+// whose first three attempts all reject (at most 0.29^3 of the draws, far
+// fewer at the couplings of a run), or whose alpha is in the Creutz range,
+// draws from the beginning, sixteen attempts at a time.  Either way the
+// lowest accepting attempt of the counter stream wins, as in the sequential
+// sampler, and the accepted attempt's arithmetic is its own.
 // ---------------------------------------------------------------------------
 constexpr int kPlaceLanes = 16;
-constexpr int kQuickHits = 4;  // attempts a record holds
+constexpr int kQuickHits = 3;              // attempts a record holds
+constexpr int kRecLanes = kQuickHits + 1;  // lanes that fill one: its attempts and its direction
 template <typename T>
 struct alignas(16) DrawRec {
     T kp[kQuickHits], r3sq[kQuickHits];
     T cos_t, sin_t, cos_p, sin_p;
 };
 
+// Share q of a record: attempt q, or the direction (q = kQuickHits).  One
+// Philox call and one cosine serve both kinds.
+template <typename T>
+__device__ __forceinline__ void fill_draw(DrawRec<T>& rec, int q, uint32_t k0, uint32_t k1, uint32_t site,
+                                          uint32_t step, uint32_t mu_sg) {
+    const bool dir = q == kQuickHits;
+    const U4 w = philox(site, step, mu_sg, dir ? RNG_DIRECTION << 24 : (RNG_ATTEMPT << 24) | (uint32_t)q, k0, k1);
+    const T u0 = uniform<T>(w.w[0]);
+    const T angle = Const<T>::two_pi * uniform<T>(w.w[1]);
+    const T c = draw_cos(angle);
+    if (dir) {
+        const T ct = T(1) - T(2) * u0;
+        rec.cos_t = ct;
+        rec.sin_t = d_sqrt(T(1) - ct * ct);
+        rec.cos_p = c;
+        rec.sin_p = draw_sin(angle);
+    } else {
+        const T r2 = uniform<T>(w.w[2]), r3 = uniform<T>(w.w[3]);
+        rec.kp[q] = -(draw_log(u0) + c * c * draw_log(r2));
+        rec.r3sq[q] = r3 * r3;
+    }
+}
+
 // The records of subgroups sg0 .. sg0 + nsteps - 1, by the sixteen lanes of
-// a place: four steps' attempts at a time, then sixteen steps' directions.
+// a place, four at a time.
 template <typename T>
 __device__ __forceinline__ void fill_draws(DrawRec<T>* rec, int nsteps, uint32_t sg0, uint32_t k0, uint32_t k1,
                                            uint32_t site, uint32_t step, uint32_t mu_hi) {
     const int q = (int)threadIdx.x % kPlaceLanes;
-    for (int t0 = 0; t0 < nsteps; t0 += kPlaceLanes / kQuickHits) {
-        const int t = t0 + q / kQuickHits, hit = q % kQuickHits;
-        if (t < nsteps) {
-            const U4 a = philox(site, step, mu_hi | (sg0 + (uint32_t)t), (RNG_ATTEMPT << 24) | (uint32_t)hit, k0, k1);
-            const T r0 = uniform<T>(a.w[0]), r1 = uniform<T>(a.w[1]), r2 = uniform<T>(a.w[2]);
-            const T r3 = uniform<T>(a.w[3]);
-            const T c = draw_cos(Const<T>::two_pi * r1);
-            rec[t].kp[hit] = -(draw_log(r0) + c * c * draw_log(r2));
-            rec[t].r3sq[hit] = r3 * r3;
-        }
-    }
-    for (int t = q; t < nsteps; t += kPlaceLanes) {
-        const U4 d = philox(site, step, mu_hi | (sg0 + (uint32_t)t), RNG_DIRECTION << 24, k0, k1);
-        const T ct = T(1) - T(2) * uniform<T>(d.w[0]);
-        const T phi = Const<T>::two_pi * uniform<T>(d.w[1]);
-        rec[t].cos_t = ct;
-        rec[t].sin_t = d_sqrt(T(1) - ct * ct);
-        rec[t].cos_p = draw_cos(phi);
-        rec[t].sin_p = draw_sin(phi);
+    for (int t0 = 0; t0 < nsteps; t0 += kPlaceLanes / kRecLanes) {
+        const int t = t0 + q / kRecLanes;
+        if (t < nsteps) fill_draw<T>(rec[t], q % kRecLanes, k0, k1, site, step, mu_hi | (sg0 + (uint32_t)t));
     }
 }
 
@@ -907,248 +380,15 @@ __device__ __forceinline__ int place_draw(T alpha, bool live, const DrawRec<T>& 
     return hit;
 }
 
-// Rows i, j of M (LDS), column c, left-multiplied by the 2x2 form of a,
-// given their current entries x = M_ic and y = M_jc.
+// One column of two rows left-multiplied by the 2x2 form of a: entries x, y
+// before, *pi, *pj after.
 template <typename T>
-__device__ __forceinline__ void rows_left_mul_col(T2<T>* M, int n, int i, int j, int c, const Quat<T>& a,
-                                                  const T2<T>& x, const T2<T>& y) {
-    M[i * n + c] = cpx<T>(fmadd(-a.q[1], y.y, fmadd(a.q[2], y.x, fmadd(-a.q[3], x.y, a.q[0] * x.x))),
-                          fmadd(a.q[1], y.x, fmadd(a.q[2], y.y, fmadd(a.q[3], x.x, a.q[0] * x.y))));
-    M[j * n + c] = cpx<T>(fmadd(a.q[3], y.y, fmadd(a.q[0], y.x, fmadd(-a.q[1], x.y, -a.q[2] * x.x))),
-                          fmadd(-a.q[3], y.x, fmadd(a.q[0], y.y, fmadd(a.q[1], x.x, -a.q[2] * x.y))));
-}
-
-// ---------------------------------------------------------------------------
-// One checkerboard phase: workgroup h updates U_mu(x), x = site h of parity
-// par.  LDS: A (staple), B0, B1 (neighbour links); the first product of each
-// staple term overwrites its left factor (B0 <- B0 B1), and after the staple
-// B1 holds U and B0 holds W = U A.
-// ---------------------------------------------------------------------------
-// RA: the staple sum (and W on its way into LDS) in registers (Acc), so that
-// LDS holds two matrices instead of three: B0 and B1, and after the staple U
-// (B1) and W (B0).  At least two waves per SIMD (at most 256 registers): the
-// FP64 form with the sum in registers would otherwise take a few more and
-// leave one.
-// NT: threads per workgroup, one wavefront or two.  With two, the loads and
-// the vector-unit products are shared by both wavefronts (RowMap: the same
-// bits), the first wavefront runs the subgroup steps, and with ho the
-// second draws their heatbath batches (below); LDS then also holds the ring
-// of two batches after the matrices (handoff_lds).
-template <typename T, bool MM, bool RA, int NT, int SW>
-__device__ __forceinline__ void update_link_wide(T2<T>* __restrict__ U, const Geom& g, int n, int mu, int par,
-                                                 int hb, T beta, uint32_t k0, uint32_t k1, uint32_t step, int h,
-                                                 bool ho) {
-    static_assert(NT == kLanes || NT == 2 * kLanes, "one wavefront or two");
-    extern __shared__ double4 smem_update[];
-    const int n2 = n * n;
-    T2<T>* A = reinterpret_cast<T2<T>*>(smem_update);  // the staple sum (without RA)
-    T2<T>* B0 = RA ? A : A + n2;
-    T2<T>* B1 = B0 + n2;
-    Acc<T, MM, NT> acc;  // the staple sum (with RA)
-    constexpr int kRows = (RA && sizeof(T) == 8) ? 2 : 4;  // FP64 with the sum in registers: fewer at a time
-    const int Vh = g.Vh;
-    const Site x = site_of(g, par, h);
-    const Site xp = step_up(g, x, mu);
-    const int op = par ^ 1;
-
-    if constexpr (RA)
-        acc.zero();
-    else
-        for (int e = threadIdx.x; e < n2; e += NT) A[e] = cpx<T>(T(0), T(0));
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu || !((g.present >> nu) & 1)) continue;
-        const Site xpn = step_up(g, x, nu), xmn = step_down(g, x, nu), xpmn = step_down(g, xp, nu);
-        // upper staple U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-        lds_load<T, T, NT>(B0, link_at<T>(U, n2, nu, op, xp.s >> 1, Vh), n, false);
-        lds_load<T, T, NT>(B1, link_at<T>(U, n2, mu, op, xpn.s >> 1, Vh), n, true);
-        __syncthreads();
-        lds_mm<T, MM, kRows, NT>(B0, B0, B1, n, false);
-        __syncthreads();
-        lds_load<T, T, NT>(B1, link_at<T>(U, n2, nu, par, h, Vh), n, true);
-        __syncthreads();
-        if constexpr (RA)
-            acc_mm<T, MM, NT>(acc, B0, B1, n);
-        else
-            lds_mm<T, MM, 4, NT>(A, B0, B1, n, true);
-        __syncthreads();
-        // lower staple U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
-        lds_load<T, T, NT>(B0, link_at<T>(U, n2, nu, par, xpmn.s >> 1, Vh), n, true);
-        lds_load<T, T, NT>(B1, link_at<T>(U, n2, mu, op, xmn.s >> 1, Vh), n, true);
-        __syncthreads();
-        lds_mm<T, MM, kRows, NT>(B0, B0, B1, n, false);
-        __syncthreads();
-        lds_load<T, T, NT>(B1, link_at<T>(U, n2, nu, op, xmn.s >> 1, Vh), n, false);
-        __syncthreads();
-        if constexpr (RA)
-            acc_mm<T, MM, NT>(acc, B0, B1, n);
-        else
-            lds_mm<T, MM, 4, NT>(A, B0, B1, n, true);
-        __syncthreads();
-    }
-    T2<T>* Us = B1;
-    lds_load<T, T, NT>(Us, link_at<T>(U, n2, mu, par, h, Vh), n, false);
-    T2<T>* W = B0;  // W = U A
-    if constexpr (RA) {
-        acc_store<T, MM, NT>(B0, acc, n);  // A into B0, which the last staple product has finished reading
-        __syncthreads();
-        acc.zero();
-        acc_mm<T, MM, NT>(acc, Us, B0, n);
-        __syncthreads();                   // every lane has read A
-        acc_store<T, MM, NT>(W, acc, n);
-    } else {
-        __syncthreads();
-        lds_mm<T, MM, 4, NT>(W, Us, A, n, false);
-    }
-    __syncthreads();
-    // With two wavefronts the subgroup steps are the first's.  With the
-    // hand-off the second draws the heatbath batches (whose Philox passes,
-    // logarithms and cosines would otherwise sit on the chain at the first
-    // step slot of each batch): batch 0 before the chain, batch b + 1 after barrier b,
-    // into slot (b + 1) mod 2 of a ring after the matrices, which the first
-    // read (into registers) before barrier b.  The first takes barrier b at
-    // step slot kSlotsPerBatch b, then reads ring slot b mod 2.  Both
-    // wavefronts pass the same ceil(S / kSlotsPerBatch) barriers, S the
-    // number of step slots.  Without it the first wavefront draws its own,
-    // as with one wavefront.  FP64 always hands off with two wavefronts
-    // (decided at compile time: keeping both draw paths in the FP64 kernel
-    // costs it 3-4%); FP32 as ho says.
-    const bool hand_off = NT > kLanes && (sizeof(T) == 8 || ho);
-    T* const ring = reinterpret_cast<T*>(reinterpret_cast<char*>(smem_update) + (RA ? 2 : 3) * n2 * sizeof(T2<T>));
-    constexpr int kSlotSteps = SW, kStepLanes = SlotShape<SW>::kStepLanes, kStepCols = SlotShape<SW>::kStepCols;
-    constexpr int kSlotWords = SlotShape<SW>::kWords, kSlotsPerBatch = SlotShape<SW>::kPerBatch;
-    uint32_t win[kPairWindows];
-    int nslot = 0;
-    pair_windows<SW>(n, win, nslot);
-    const int nbatch = (nslot + kSlotsPerBatch - 1) / kSlotsPerBatch;
-    if (NT > kLanes && threadIdx.x >= kLanes) {
-        if (hand_off && hb) {
-            const uint32_t l = threadIdx.x - kLanes;
-            const uint32_t mh = (uint32_t)mu << 16;
-            ring_store<T>(ring, 0, (int)l, draw_pair_batch<T>(k0, k1, (uint32_t)x.s, step, mh, win[0], 0, n, l));
-            for (int b = 0; b < nbatch; ++b) {
-                __syncthreads();
-                const int wb = kBatchWords * (b + 1);  // the next batch's first table word
-                if (b + 1 < nbatch) {
-                    if ((wb & (kLanes - 1)) == 0) pair_windows_shift(win);
-                    ring_store<T>(ring, (b + 1) & 1, (int)l,
-                                  draw_pair_batch<T>(k0, k1, (uint32_t)x.s, step, mh, win[0], wb & (kLanes - 1), n, l));
-                }
-            }
-        }
-        __syncthreads();
-        T2<T>* dst = const_cast<T2<T>*>(link_at<T>(U, n2, mu, par, h, Vh));
-        for (int e = threadIdx.x; e < n2; e += NT) dst[e] = Us[e];
-        return;
-    }
-
-    const int lane = threadIdx.x;
-    const uint32_t mu_hi = (uint32_t)mu << 16;
-    DrawBatch<T> batch{};
-    const T cb = T(2) * beta / T(n);  // alpha = 2 beta k / n
-    // The slots are ordered by wave_lds_order; in each, lane l runs place
-    // l / kStepLanes, owning columns l mod kStepLanes + k kStepLanes of U and
-    // of W and reading its entries of rows i and j together with the 2x2
-    // block.  A slot's places are filled first, so place 0 always holds a
-    // step; the lanes of an empty place read that step's rows and write
-    // nothing.
-    const int place = lane / kStepLanes;
-    const int c0 = lane % kStepLanes;
-    for (int t = 0; t < nslot; ++t) {
-        const int u = (t * kSlotWords) & (kLanes - 1);
-        if (u == 0 && t > 0) pair_windows_shift(win);
-        uint32_t wd[kSlotWords], stp[kSlotSteps];
-        int np = 0;
-#pragma unroll
-        for (int k = 0; k < kSlotWords; ++k) wd[k] = pair_at(win[0], u + k);
-#pragma unroll
-        for (int m = 0; m < kSlotSteps; ++m) {
-            stp[m] = (wd[m / 2] >> (16 * (m % 2))) & 0xFFFFu;
-            np += stp[m] != pairs::kNoStep;
-        }
-        uint32_t es = stp[0];
-#pragma unroll
-        for (int m = 1; m < kSlotSteps; ++m)
-            if (place == m && m < np) es = stp[m];
-        const bool mine = place < np;
-        const int i = (int)(es & 0xFF), j = (int)((es >> 8) & 0xFF);
-        const T2<T> wii = W[i * n + i], wij = W[i * n + j], wji = W[j * n + i], wjj = W[j * n + j];
-        T2<T> ui[kStepCols], uj[kStepCols], xi[kStepCols], xj[kStepCols];
-#pragma unroll
-        for (int cc = 0; cc < kStepCols; ++cc) {
-            const int ck = c0 + cc * kStepLanes;
-            const int c = ck < n ? ck : 0;
-            ui[cc] = Us[i * n + c];
-            uj[cc] = Us[j * n + c];
-            xi[cc] = W[i * n + c];
-            xj[cc] = W[j * n + c];
-        }
-        Quat<T> p;
-        p.q[0] = T(0.5) * (wii.x + wjj.x);
-        p.q[3] = T(0.5) * (wii.y - wjj.y);
-        p.q[2] = T(0.5) * (wij.x - wji.x);
-        p.q[1] = T(0.5) * (wij.y + wji.y);
-        Quat<T> v;
-        const T k = chain_unit_quat(p, v);
-        Quat<T> a;
-        bool apply = true;
-        if (hb) {
-            const int q = t % kSlotsPerBatch;
-            if (q == 0) {
-                if (hand_off) {
-                    __syncthreads();
-                    batch = ring_load<T>(ring, (t / kSlotsPerBatch) & 1, lane);
-                } else {
-                    batch = draw_pair_batch<T>(k0, k1, (uint32_t)x.s, step, mu_hi, win[0], u, n, (uint32_t)lane);
-                }
-            }
-            const T alpha = cb * k;
-            uint32_t sgs[kSlotSteps];
-#pragma unroll
-            for (int m = 0; m < kSlotSteps; ++m) sgs[m] = mu_hi | pair_sg(wd[m / 2], m % 2, n);
-            Quat<T> xs;
-            apply = sample_su2_slot<T, SW>(alpha, batch, q, np, k0, k1, (uint32_t)x.s, step, sgs, xs) != 0;
-            if (apply) a = qmul(xs, qconj(v));
-        } else {
-            const Quat<T> vc = qconj(v);
-            a = qmul(vc, vc);
-        }
-        if (apply && mine) {
-#pragma unroll
-            for (int cc = 0; cc < kStepCols; ++cc) {
-                const int ck = c0 + cc * kStepLanes;
-                if (ck < n) {
-                    rows_left_mul_col<T>(Us, n, i, j, ck, a, ui[cc], uj[cc]);
-                    rows_left_mul_col<T>(W, n, i, j, ck, a, xi[cc], xj[cc]);
-                }
-            }
-        }
-        wave_lds_order();
-    }
-    __syncthreads();
-    T2<T>* dst = const_cast<T2<T>*>(link_at<T>(U, n2, mu, par, h, Vh));
-    for (int e = threadIdx.x; e < n2; e += NT) dst[e] = Us[e];
-}
-
-// One checkerboard phase of one lattice: workgroup h updates link h.
-template <typename T, bool MM, bool RA, int NT, int SW>
-__global__ __launch_bounds__(NT, 2) void k_update(T2<T>* __restrict__ U, Geom g, int n, int mu, int par, int hb,
-                                               T beta, uint32_t k0, uint32_t k1, uint32_t step, int ho) {
-    update_link_wide<T, MM, RA, NT, SW>(U, g, n, mu, par, hb, beta, k0, k1, step, (int)blockIdx.x, ho != 0);
-}
-
-// One phase of every chain of a batch group (same Nc and precision): one
-// workgroup per updated link of each chain, the chain found by binary search
-// over the first-link prefix of the descriptor table (TILE_HALF_HB counts
-// links here); coupling, Philox key and RNG step come from the table.
-template <typename T, bool MM, bool RA, int NT, int SW>
-__global__ __launch_bounds__(NT, 2) void k_update_batch(const ChainDesc* __restrict__ d, int nchains, int n,
-                                                     int mu, int par, int hb, uint32_t step_offset, int ho) {
-    const int c = find_chain<TILE_HALF_HB>(d, nchains, (int)blockIdx.x);
-    const Geom g = d[c].g;
-    if (!((g.present >> mu) & 1)) return;
-    update_link_wide<T, MM, RA, NT, SW>((T2<T>*)d[c].links, g, n, mu, par, hb, (T)d[c].beta, d[c].k0, d[c].k1,
-                                (uint32_t)(d[c].step + step_offset), (int)blockIdx.x - d[c].tile0[TILE_HALF_HB],
-                                ho != 0);
+__device__ __forceinline__ void rows_left_mul_at(T2<T>* pi, T2<T>* pj, const Quat<T>& a, const T2<T>& x,
+                                                 const T2<T>& y) {
+    *pi = cpx<T>(fmadd(-a.q[1], y.y, fmadd(a.q[2], y.x, fmadd(-a.q[3], x.y, a.q[0] * x.x))),
+                 fmadd(a.q[1], y.x, fmadd(a.q[2], y.y, fmadd(a.q[3], x.x, a.q[0] * x.y))));
+    *pj = cpx<T>(fmadd(a.q[3], y.y, fmadd(a.q[0], y.x, fmadd(-a.q[1], x.y, -a.q[2] * x.x))),
+                 fmadd(-a.q[3], y.x, fmadd(a.q[0], y.y, fmadd(a.q[1], x.x, -a.q[2] * x.y))));
 }
 
 // ---------------------------------------------------------------------------
@@ -1384,7 +624,7 @@ __device__ __forceinline__ void reunit_link_wide(T2<T>* __restrict__ U, const Ge
     double du = 0.0, dd = 0.0;
     if ((g.present >> mu) & 1) {
         const T2<T>* src = link_at<T>(U, n2, mu, par, h, g.Vh);
-        lds_load<double, T>(M, src, n, false);
+        lds_load<double, T>(M, src, n);
         __syncthreads();
         if (REPORT) du = lds_unitarity_dev(M, n);
         __syncthreads();
@@ -1392,7 +632,7 @@ __device__ __forceinline__ void reunit_link_wide(T2<T>* __restrict__ U, const Ge
         lds_det(M, n, dr, di);
         if (REPORT) dd = nan_to_inf(sqrt(fmadd(di, di, (dr - 1.0) * (dr - 1.0))));
         __syncthreads();
-        lds_load<double, T>(M, src, n, false);
+        lds_load<double, T>(M, src, n);
         __syncthreads();
         lds_reunit(M, P, n, dr, di);
         T2<T>* dst = const_cast<T2<T>*>(src);
@@ -1429,7 +669,7 @@ __global__ __launch_bounds__(kLanes) void k_unitarity(const T2<T>* __restrict__ 
     link_id(g, id, mu, par, h);
     double du = 0.0, dd = 0.0;
     if ((g.present >> mu) & 1) {
-        lds_load<double, T>(M, link_at<T>(U, n2, mu, par, h, g.Vh), n, false);
+        lds_load<double, T>(M, link_at<T>(U, n2, mu, par, h, g.Vh), n);
         __syncthreads();
         du = lds_unitarity_dev(M, n);
         __syncthreads();
@@ -1516,13 +756,13 @@ __device__ __forceinline__ void plaquette_site_wide(const T2<T>* __restrict__ U,
         for (int nu = mu + 1; nu < 4; ++nu) {
             if (!((g.present >> mu) & 1) || !((g.present >> nu) & 1)) continue;
             const Site xm = step_up(g, x, mu), xn = step_up(g, x, nu);
-            lds_load<double, T>(X, link_at<T>(U, n2, mu, par, h, g.Vh), n, false);
-            lds_load<double, T>(Y, link_at<T>(U, n2, nu, op, xm.s >> 1, g.Vh), n, false);
+            lds_load<double, T>(X, link_at<T>(U, n2, mu, par, h, g.Vh), n);
+            lds_load<double, T>(Y, link_at<T>(U, n2, nu, op, xm.s >> 1, g.Vh), n);
             __syncthreads();
             lds_mm<double>(A, X, Y, n, false);
             __syncthreads();
-            lds_load<double, T>(X, link_at<T>(U, n2, nu, par, h, g.Vh), n, false);
-            lds_load<double, T>(Y, link_at<T>(U, n2, mu, op, xn.s >> 1, g.Vh), n, false);
+            lds_load<double, T>(X, link_at<T>(U, n2, nu, par, h, g.Vh), n);
+            lds_load<double, T>(Y, link_at<T>(U, n2, mu, op, xn.s >> 1, g.Vh), n);
             __syncthreads();
             double t = 0.0;
             for (int e = threadIdx.x; e < n2; e += kLanes) {
@@ -1601,7 +841,7 @@ __global__ __launch_bounds__(kLanes) void k_polyakov(const T2<T>* __restrict__ U
             r = q;
         }
         st.s = s;
-        lds_load<double, T>(X, link_at<T>(U, n2, 3, parity_of(st), s >> 1, g.Vh), n, false);
+        lds_load<double, T>(X, link_at<T>(U, n2, 3, parity_of(st), s >> 1, g.Vh), n);
         __syncthreads();
         lds_mm<double>(Tm, P, X, n, false);
         __syncthreads();
@@ -1655,23 +895,26 @@ __global__ __launch_bounds__(256) void k_import(T2<T>* __restrict__ U, Geom g, i
 }
 
 // ---------------------------------------------------------------------------
-// The batched SU(2) draw alone, for parity tests: element i is subgroup
-// mu_sg + (i mod 8) of site i / 8, drawn as the update draws it (one batch
-// per site, the slots in order).  dev_x gets 4n doubles, attempts n ints
-// (the accepted attempt's number, 0 when all were rejected).
+// The draw by place alone, for parity tests: element i is subgroup mu_sg +
+// (i mod 8) of site i / 8.  dev_x gets 4n doubles, attempts n ints (the
+// accepted attempt's number, 0 when all were rejected).
 // ---------------------------------------------------------------------------
+constexpr int kSampleSteps = 8;  // subgroups per site (and workgroup)
 template <typename T>
 __global__ __launch_bounds__(kLanes) void k_sample_su2_batched(const double* __restrict__ alpha, int n, uint32_t k0,
                                                                uint32_t k1, uint32_t step, uint32_t mu_sg,
                                                                double* __restrict__ x, int* __restrict__ attempts) {
+    __shared__ DrawRec<T> rec[kSampleSteps];
     const uint32_t site = blockIdx.x;
-    const DrawBatch<T> b = draw_batch<T>(k0, k1, site, step, 0u, mu_sg, threadIdx.x);
-    for (int s = 0; s < kSgBatch; ++s) {
-        const int i = (int)site * kSgBatch + s;
-        if (i >= n) break;
-        Quat<T> q{{T(1), T(0), T(0), T(0)}};
-        const int a = sample_su2_lanes<T>((T)alpha[i], b, s, k0, k1, site, step, mu_sg + (uint32_t)s, q);
-        if (threadIdx.x == 0) {
+    if (threadIdx.x < kPlaceLanes) fill_draws<T>(rec, kSampleSteps, mu_sg, k0, k1, site, step, 0u);
+    __syncthreads();
+    constexpr int kPlaces = kLanes / kPlaceLanes;
+    for (int s0 = 0; s0 < kSampleSteps; s0 += kPlaces) {
+        const int s = s0 + (int)threadIdx.x / kPlaceLanes, i = (int)site * kSampleSteps + s;
+        Quat<T> q;
+        const int a = place_draw<T>(i < n ? (T)alpha[i] : T(1), i < n, rec[s], k0, k1, site, step, mu_sg + (uint32_t)s, q);
+        if (i < n && threadIdx.x % kPlaceLanes == 0) {
+            if (a == 0) q = Quat<T>{{T(1), T(0), T(0), T(0)}};
 #pragma unroll
             for (int c = 0; c < 4; ++c) x[4 * (size_t)i + c] = q.q[c];
             attempts[i] = a;

@@ -292,7 +292,7 @@ __device__ __forceinline__ void update_links_small(T2<T>* __restrict__ U, const 
                 const Quat<T> vc = qconj(v);
                 a = qmul(vc, vc);
             }
-            if (apply && r8 < N) rows_left_mul_col<T>(col, kRow, i, j, 0, a, ci, cj);
+            if (apply && r8 < N) rows_left_mul_at<T>(col + i * kRow, col + j * kRow, a, ci, cj);
             wave_lds_order();
         }
     if (live) {

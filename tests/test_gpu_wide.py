@@ -377,3 +377,23 @@ def test_wide_four_links_per_wavefront(gpu, nc, dtype, L):
         want = before.copy()
         m, k = oracle_phase_diag(want, nc, L, kind, mu, par, beta, 13, 4)
         compare_links(got, want, dtype, m, k, f"nc={nc} {dtype} kind={kind} beta={beta}", spread=sp)
+
+
+@pytest.mark.parametrize("nc,dtype", [(10, "f32"), (15, "f64"), (17, "f32"), (17, "f64"), (20, "f32"), (25, "f32"),
+                                      (25, "f64"), (26, "f32"), (26, "f64"), (31, "f32"), (31, "f64")])
+def test_wide_two_wavefronts_at_the_edges_of_their_ranges(gpu, nc, dtype):
+    """From Nc = 9 a link has two wavefronts and matrix-core tiles: the first
+    and last Nc of each tile form, odd ones (whose products end on a padded
+    k) among them, and a coupling in the draws' Creutz range."""
+    L = (4, 2, 2, 2)
+    base = O.new_field(nc, L, hot=True, seed=61)
+    lat = gpu_lattice(gpu, nc, L, dtype, field=base)
+    for kind, mu, par, beta in [(0, 0, 1, beta_for(nc)), (0, 1, 0, 0.3 * nc), (1, 3, 1, 1.0)]:
+        before = to_np(lat.export())
+        lat.phase(kind, mu, par, beta, seed=17, step=6)
+        got = to_np(lat.export())
+        sp = twin_spread(before, nc, L, kind, mu, par, beta, 17, 6, rel=REL[dtype[:3]])
+        want = before.copy()
+        m, k = oracle_phase_diag(want, nc, L, kind, mu, par, beta, 17, 6)
+        dec = (np.prod(L) // 2) * nc * (nc - 1) // 2 if kind == 0 else None
+        compare_links(got, want, dtype, m, k, f"nc={nc} {dtype} kind={kind} beta={beta}", spread=sp, decisions=dec)
