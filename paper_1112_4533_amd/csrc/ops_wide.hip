@@ -36,8 +36,7 @@ struct OpsWide {
         return 4 * c.g.V;
     }
     static int plaquette(const Ctx& c, double* partial) {
-        wide::k_plaquette<T><<<c.g.V, wide::kLanes, wide::fp64_lds(c.nc, 3), c.stream>>>((const P*)c.links, c.g, c.nc,
-                                                                                         partial);
+        launch_plaquette_wide<T>(c, partial);
         return c.g.V;
     }
     static int polyakov(const Ctx& c, double* partial) {
@@ -71,7 +70,7 @@ struct OpsWide {
             d, n, nc);
     }
     static void plaquette_batch(const ChainDesc* d, int n, int tiles, double* out, int nc, hipStream_t s) {
-        wide::k_plaquette_batch<T><<<tiles, wide::kLanes, wide::fp64_lds(nc, 3), s>>>(d, n, nc);
+        launch_plaquette_wide_batch<T>(d, n, tiles, nc, s);
         wide::k_plaquette_final_batch_wide<><<<n, kBlock, 0, s>>>(d, n, nc, out);
     }
 

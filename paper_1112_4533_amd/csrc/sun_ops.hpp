@@ -149,6 +149,14 @@ constexpr int kWideSmallMax = 8, kWideSmallLinks = 4;
 inline int wide_update_tiles(int nc, int Vh) {
     return nc <= kWideSmallMax ? (Vh + kWideSmallLinks - 1) / kWideSmallLinks : Vh;
 }
+// Likewise the plaquette takes kWideSmallLinks sites, or one.
+inline int wide_plaquette_tiles(int nc, int V) {
+    return nc <= kWideSmallMax ? (V + kWideSmallLinks - 1) / kWideSmallLinks : V;
+}
+template <typename T>
+void launch_plaquette_wide(const Ctx& c, double* partial);
+template <typename T>
+void launch_plaquette_wide_batch(const ChainDesc* d, int n, int tiles, int nc, hipStream_t s);
 template <typename T>
 void launch_update_small(const Ctx& c, int hb, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step);
 template <typename T>

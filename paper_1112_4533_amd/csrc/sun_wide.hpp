@@ -153,6 +153,19 @@ __device__ __forceinline__ void lds_mm(T2<T>* C, const T2<T>* A, const T2<T>* B,
         lds_mm_rows<T, 1>(C, A, B, n, acc, g, j, i0, cnt);
 }
 
+// Change of the site index by one step along direction m (periodic), and the
+// value of a run-time direction picked with selects (an array indexed by it
+// would live in memory).
+__device__ __forceinline__ int step_shift(const Geom& g, const Site& x, bool up, int m) {
+    const int wrap = (g.L[m] - 1) * g.stride[m];
+    return up ? (x.x[m] == g.L[m] - 1 ? -wrap : g.stride[m]) : (x.x[m] == 0 ? wrap : -g.stride[m]);
+}
+__device__ __forceinline__ int pick_dir(int a, int b, int c, int d, int m) {
+    int v = m == 1 ? b : a;
+    v = m == 2 ? c : v;
+    return m == 3 ? d : v;
+}
+
 // Cross-lane moves of a wavefront without the LDS: lane l receives the
 // value of its partner lane, for five pairings that together join all 64
 // lanes -- l xor 1 and l xor 2 (quad permutes), 7 - l and 15 - l within
@@ -167,7 +180,7 @@ __device__ __forceinline__ int partner(int v) {
     if constexpr (STEP == 4) return __builtin_amdgcn_ds_swizzle(v, 0x401F);                     // xor 16
     if constexpr (STEP == 5) {                                                                   // xor 32
         const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        return threadIdx.x < 32 ? (int)r[1] : (int)r[0];
+        return (threadIdx.x & (kLanes - 1)) < 32 ? (int)r[1] : (int)r[0];
     }
     return v;
 }
@@ -725,78 +738,6 @@ __global__ __launch_bounds__(kLanes) void k_init(T2<T>* __restrict__ U, Geom g, 
     }
     T2<T>* dst = const_cast<T2<T>*>(link_at<T>(U, n2, mu, par, h, g.Vh));
     for (int e = threadIdx.x; e < n2; e += kLanes) dst[e] = cpx<T>((T)M[e].x, (T)M[e].y);
-}
-
-// Plaquettes of site blockIdx.x (logical order): partial[2 s] = sum over the
-// planes without direction 3, partial[2 s + 1] = with direction 3, FP64.
-// ReTr(U_mu(x) U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag) = Re sum_ij A_ij conj(B_ij)
-// with A = U_mu(x) U_nu(x+mu), B = U_nu(x) U_mu(x+nu).  LDS: A, X, Y.
-template <typename T>
-__device__ __forceinline__ void plaquette_site_wide(const T2<T>* __restrict__ U, const Geom& g, int n, int s,
-                                                    double* __restrict__ partial) {
-    extern __shared__ double4 smem_plaq[];
-    const int n2 = n * n;
-    double2* A = reinterpret_cast<double2*>(smem_plaq);
-    double2* X = A + n2;
-    double2* Y = X + n2;
-    Site x;
-    {
-        int r = s;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int q = r / g.L[m];
-            x.x[m] = r - q * g.L[m];
-            r = q;
-        }
-        x.s = s;
-    }
-    const int par = parity_of(x), op = par ^ 1, h = s >> 1;
-    double acc[2] = {0.0, 0.0};
-    for (int mu = 0; mu < 4; ++mu)
-        for (int nu = mu + 1; nu < 4; ++nu) {
-            if (!((g.present >> mu) & 1) || !((g.present >> nu) & 1)) continue;
-            const Site xm = step_up(g, x, mu), xn = step_up(g, x, nu);
-            lds_load<double, T>(X, link_at<T>(U, n2, mu, par, h, g.Vh), n);
-            lds_load<double, T>(Y, link_at<T>(U, n2, nu, op, xm.s >> 1, g.Vh), n);
-            __syncthreads();
-            lds_mm<double>(A, X, Y, n, false);
-            __syncthreads();
-            lds_load<double, T>(X, link_at<T>(U, n2, nu, par, h, g.Vh), n);
-            lds_load<double, T>(Y, link_at<T>(U, n2, mu, op, xn.s >> 1, g.Vh), n);
-            __syncthreads();
-            double t = 0.0;
-            for (int e = threadIdx.x; e < n2; e += kLanes) {
-                const int i = e / n, j = e - i * n;
-                double br = 0.0, bi = 0.0;
-                for (int k = 0; k < n; ++k) {
-                    const double2 a = X[i * n + k], b = Y[k * n + j];
-                    cmac(br, bi, a.x, a.y, b.x, b.y);
-                }
-                t = fmadd(A[e].y, bi, fmadd(A[e].x, br, t));
-            }
-            acc[nu == 3 ? 1 : 0] += wave_sum(t);
-            __syncthreads();
-        }
-    if (threadIdx.x == 0) {
-        partial[2 * (size_t)s] = acc[0];
-        partial[2 * (size_t)s + 1] = acc[1];
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kLanes) void k_plaquette(const T2<T>* __restrict__ U, Geom g, int n,
-                                                      double* __restrict__ partial) {
-    plaquette_site_wide<T>(U, g, n, (int)blockIdx.x, partial);
-}
-
-// Plaquette sums of every chain of a batch group: one workgroup per site
-// (TILE_SITE counts sites here), the partials in each chain's own scratch at
-// the index the single-lattice kernel uses.
-template <typename T>
-__global__ __launch_bounds__(kLanes) void k_plaquette_batch(const ChainDesc* __restrict__ d, int nchains, int n) {
-    const int c = find_chain<TILE_SITE>(d, nchains, (int)blockIdx.x);
-    plaquette_site_wide<T>((const T2<T>*)d[c].links, d[c].g, n, (int)blockIdx.x - d[c].tile0[TILE_SITE],
-                           d[c].scratch);
 }
 
 // One block per chain: out[3 c .. 3 c + 2] from its V site partials.

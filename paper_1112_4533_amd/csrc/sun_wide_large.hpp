@@ -74,33 +74,33 @@ static __constant__ pairs::Table<kSlotSteps> kSlotTable = pairs::make_table<kSlo
 // e / n for e < 1024, n <= 32, from inv = ceil(2^16 / n)
 __device__ __forceinline__ int div_by(int e, int inv) { return (e * inv) >> 16; }
 
-// Places of the entries threadIdx.x + 128 c of a link in an LDS matrix; those
-// past the link's end go to the entry that holds none.
-template <int LOADS>
+// Places of the entries threadIdx.x + THREADS c of a link in an LDS matrix;
+// those past the link's end go to the entry that holds none.
+template <int LOADS, int THREADS = kLargeThreads>
 struct Places {
     int at[LOADS];
     __device__ __forceinline__ Places(int n, int n2) {
         const int inv = ((1 << 16) + n - 1) / n, pad = row_stride(n) - n;
 #pragma unroll
         for (int c = 0; c < LOADS; ++c) {
-            const int e = (int)threadIdx.x + c * kLargeThreads;
+            const int e = (int)threadIdx.x + c * THREADS;
             at[c] = e < n2 ? e + pad * div_by(e, inv) : mat_entries(n) - 1;
         }
     }
 };
 // Those entries of one link, in registers.
-template <typename T, int LOADS>
+template <typename T, int LOADS, int THREADS = kLargeThreads>
 struct LinkPart {
     T re[LOADS], im[LOADS];
     __device__ __forceinline__ void load(const T2<T>* __restrict__ src, int n2) {
 #pragma unroll
         for (int c = 0; c < LOADS; ++c) {
-            const T2<T> v = src[min((unsigned)threadIdx.x + c * kLargeThreads, (unsigned)n2 - 1)];
+            const T2<T> v = src[min((unsigned)threadIdx.x + c * THREADS, (unsigned)n2 - 1)];
             re[c] = v.x;
             im[c] = v.y;
         }
     }
-    __device__ __forceinline__ void store(T2<T>* dst, const Places<LOADS>& pl) const {
+    __device__ __forceinline__ void store(T2<T>* dst, const Places<LOADS, THREADS>& pl) const {
 #pragma unroll
         for (int c = 0; c < LOADS; ++c) dst[pl.at[c]] = cpx<T>(re[c], im[c]);
     }
@@ -248,13 +248,12 @@ struct Product<float, true> {
 };
 
 // FP64, 16 < Nc: four 16 x 16 tiles, rows 0 .. 15 on the first wavefront, the
-// others on the second, each lane reading whole complex entries for the
-// real and the imaginary tiles.
+// others on the second.
 template <>
 struct Product<double, true> {
     f64x4 re[2], im[2];
     struct Ops {
-        double2 a, b0, b1;
+        double a, same0, other0, same1, other1;
     };
     __device__ __forceinline__ void zero() {
 #pragma unroll
@@ -266,22 +265,25 @@ struct Product<double, true> {
         const int part = (l >> 4) & 1, kk = l >> 5;
         const int ra = min(kTile * w + (l & 15), n - 1);
         const int c0 = l & 15, c1 = min(kTile + (l & 15), n - 1);
-        const double2* a = A + (DA ? ra + kk * ns : ra * ns + kk);
-        const double2* b0 = B + (DB ? c0 * ns + kk : c0 + kk * ns);
-        const double2* b1 = B + (DB ? c1 * ns + kk : c1 + kk * ns);
-        const int da = DA ? 2 * ns : 2, db = DB ? 2 : 2 * ns;
-        auto term = [&](const double2& av, const double2& b0v, const double2& b1v) {
-            const double ai = DA ? -av.y : av.y;
-            const double ar = part ? -ai : av.x, am = part ? ai : av.x;
-            const double p0 = DB ? -b0v.y : b0v.y, p1 = DB ? -b1v.y : b1v.y;
-            re[0] = mma16(ar, part ? p0 : b0v.x, re[0]);
-            im[0] = mma16(am, part ? b0v.x : p0, im[0]);
-            re[1] = mma16(ar, part ? p1 : b1v.x, re[1]);
-            im[1] = mma16(am, part ? b1v.x : p1, im[1]);
-        };
-        const int pairs = (n + 1) >> 1;
-        for_steps<1>(pairs, [&](int s) { return Ops{a[s * da], b0[s * db], b1[s * db]}; },
-                     [&](const Ops& o) { term(o.a, o.b0, o.b1); });
+        // re takes a_re b_re and -a_im b_im, im a_re b_im and a_im b_re: the
+        // lane's part of A serves both, signs collected on it and on B's im
+        const double* a = reinterpret_cast<const double*>(A + (DA ? ra + kk * ns : ra * ns + kk)) + part;
+        const double* b0 = reinterpret_cast<const double*>(B + (DB ? c0 * ns + kk : c0 + kk * ns));
+        const double* b1 = reinterpret_cast<const double*>(B + (DB ? c1 * ns + kk : c1 + kk * ns));
+        const int da = DA ? 4 * ns : 4, db = DB ? 4 : 4 * ns;
+        const bool neg_re = part && (!DA ^ DB), neg_im = (part && DA) ^ (!part && DB);
+        for_steps<1>((n + 1) >> 1,
+                     [&](int s) {
+                         return Ops{a[s * da], b0[s * db + part], b0[s * db + 1 - part], b1[s * db + part],
+                                    b1[s * db + 1 - part]};
+                     },
+                     [&](const Ops& o) {
+                         const double ar = neg_re ? -o.a : o.a, am = neg_im ? -o.a : o.a;
+                         re[0] = mma16(ar, o.same0, re[0]);
+                         im[0] = mma16(am, o.other0, im[0]);
+                         re[1] = mma16(ar, o.same1, re[1]);
+                         im[1] = mma16(am, o.other1, im[1]);
+                     });
     }
     __device__ __forceinline__ void store(double2* C, int n, int ns, int w) const {
         const int l = fresh_lane();
@@ -351,19 +353,10 @@ __device__ __forceinline__ void update_link_large(T2<T>* __restrict__ U, const G
     const int op = par ^ 1;
     // The site and its neighbours are the workgroup's: scalar registers.
     const int xs = __builtin_amdgcn_readfirstlane(x.s);
-    auto shift = [&](int up, int m) {  // change of the site index by one step
-        const int wrap = (g.L[m] - 1) * g.stride[m];
-        const int v = up ? (x.x[m] == g.L[m] - 1 ? -wrap : g.stride[m]) : (x.x[m] == 0 ? wrap : -g.stride[m]);
-        return __builtin_amdgcn_readfirstlane(v);
-    };
-    auto pick = [](int a, int b, int c, int d, int m) {
-        int v = m == 1 ? b : a;
-        v = m == 2 ? c : v;
-        return m == 3 ? d : v;
-    };
-    const int u0 = shift(1, 0), u1 = shift(1, 1), u2 = shift(1, 2), u3 = shift(1, 3);
-    const int d0 = shift(0, 0), d1 = shift(0, 1), d2 = shift(0, 2), d3 = shift(0, 3);
-    const int sp = xs + pick(u0, u1, u2, u3, mu);  // x + mu
+    auto shift = [&](bool up, int m) { return __builtin_amdgcn_readfirstlane(step_shift(g, x, up, m)); };
+    const int u0 = shift(true, 0), u1 = shift(true, 1), u2 = shift(true, 2), u3 = shift(true, 3);
+    const int d0 = shift(false, 0), d1 = shift(false, 1), d2 = shift(false, 2), d3 = shift(false, 3);
+    const int sp = xs + pick_dir(u0, u1, u2, u3, mu);  // x + mu
     auto next_dir = [&](int nu) {
         do ++nu;
         while (nu < 4 && (nu == mu || !((g.present >> nu) & 1)));
@@ -373,10 +366,10 @@ __device__ __forceinline__ void update_link_large(T2<T>* __restrict__ U, const G
     LinkPart<T, kLoads> fa, fb;
     auto load_upper = [&](int nu) {
         fa.load(link_at<T>(U, n2, nu, op, sp >> 1, Vh), n2);
-        fb.load(link_at<T>(U, n2, mu, op, (xs + pick(u0, u1, u2, u3, nu)) >> 1, Vh), n2);
+        fb.load(link_at<T>(U, n2, mu, op, (xs + pick_dir(u0, u1, u2, u3, nu)) >> 1, Vh), n2);
     };
     auto load_lower = [&](int nu) {
-        const int sh = pick(d0, d1, d2, d3, nu);  // the same from x + mu: nu is another direction
+        const int sh = pick_dir(d0, d1, d2, d3, nu);  // the same from x + mu: nu is another direction
         fa.load(link_at<T>(U, n2, nu, par, (sp + sh) >> 1, Vh), n2);
         fb.load(link_at<T>(U, n2, mu, op, (xs + sh) >> 1, Vh), n2);
     };
@@ -409,7 +402,7 @@ __device__ __forceinline__ void update_link_large(T2<T>* __restrict__ U, const G
         // lower staple U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
         fa.store(B0, pl);
         fb.store(B1, pl);
-        fb.load(link_at<T>(U, n2, nu, op, (xs + pick(d0, d1, d2, d3, nu)) >> 1, Vh), n2);
+        fb.load(link_at<T>(U, n2, nu, op, (xs + pick_dir(d0, d1, d2, d3, nu)) >> 1, Vh), n2);
         __syncthreads();
         m.zero();
         m.template add<true, true>(B0, B1, n, ns, w);

@@ -142,33 +142,23 @@ __device__ __forceinline__ void update_links_small(T2<T>* __restrict__ U, const 
     const int Vh = g.Vh;
     const Site x = site_of(g, par, h);
     const int op = par ^ 1;
-    // changes of the site index by one step up and down each direction; the
-    // direction is a run-time value, picked with selects so that no array is
-    // indexed by it
-    auto shift = [&](int up, int m) {
-        const int wrap = (g.L[m] - 1) * g.stride[m];
-        return up ? (x.x[m] == g.L[m] - 1 ? -wrap : g.stride[m]) : (x.x[m] == 0 ? wrap : -g.stride[m]);
-    };
-    auto pick = [](int a, int b, int c, int d, int m) {
-        int v = m == 1 ? b : a;
-        v = m == 2 ? c : v;
-        return m == 3 ? d : v;
-    };
-    const int u0 = shift(1, 0), u1 = shift(1, 1), u2 = shift(1, 2), u3 = shift(1, 3);
-    const int d0 = shift(0, 0), d1 = shift(0, 1), d2 = shift(0, 2), d3 = shift(0, 3);
-    const int sp = x.s + pick(u0, u1, u2, u3, mu);  // x + mu
+    const int u0 = step_shift(g, x, true, 0), u1 = step_shift(g, x, true, 1);
+    const int u2 = step_shift(g, x, true, 2), u3 = step_shift(g, x, true, 3);
+    const int d0 = step_shift(g, x, false, 0), d1 = step_shift(g, x, false, 1);
+    const int d2 = step_shift(g, x, false, 2), d3 = step_shift(g, x, false, 3);
+    const int sp = x.s + pick_dir(u0, u1, u2, u3, mu);  // x + mu
 
     // Loads run one staple term ahead of the arithmetic, in the registers of
     // the sixteen lanes.
     LinkRegs<T, N> fl, fq, fr;
     auto load_upper = [&](int nu) {
-        const int spn = x.s + pick(u0, u1, u2, u3, nu);
+        const int spn = x.s + pick_dir(u0, u1, u2, u3, nu);
         fl.load(link_at<T>(U, n2, nu, op, sp >> 1, Vh), q);
         fq.load(link_at<T>(U, n2, mu, op, spn >> 1, Vh), q);
         fr.load(link_at<T>(U, n2, nu, par, h, Vh), q);
     };
     auto load_lower = [&](int nu) {
-        const int sh = pick(d0, d1, d2, d3, nu);  // the same from x + mu: nu is another direction
+        const int sh = pick_dir(d0, d1, d2, d3, nu);  // the same from x + mu: nu is another direction
         const int smn = x.s + sh;
         fl.load(link_at<T>(U, n2, nu, par, (sp + sh) >> 1, Vh), q);
         fq.load(link_at<T>(U, n2, mu, op, smn >> 1, Vh), q);

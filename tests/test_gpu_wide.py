@@ -397,3 +397,14 @@ def test_wide_two_wavefronts_at_the_edges_of_their_ranges(gpu, nc, dtype):
         m, k = oracle_phase_diag(want, nc, L, kind, mu, par, beta, 17, 6)
         dec = (np.prod(L) // 2) * nc * (nc - 1) // 2 if kind == 0 else None
         compare_links(got, want, dtype, m, k, f"nc={nc} {dtype} kind={kind} beta={beta}", spread=sp, decisions=dec)
+
+
+@pytest.mark.parametrize("nc,dtype,L", [(5, "f32", (6, 2, 1, 2)), (6, "f64", (2, 2, 2, 2)), (7, "f32", (4, 2, 2, 2)),
+                                        (8, "f64", (6, 2, 1, 1)), (12, "f32", (4, 2, 2, 2)), (17, "f64", (2, 2, 2, 2)),
+                                        (20, "f32", (2, 2, 2, 2)), (25, "f64", (2, 2, 1, 2)), (31, "f32", (2, 2, 2, 2))])
+def test_wide_plaquette_of_every_tile_form(gpu, nc, dtype, L):
+    """The plaquette where four sites share a wavefront (Nc <= 8), on one
+    tile (<= 16) and on four, odd Nc and absent directions among them."""
+    lat = gpu_lattice(gpu, nc, L, dtype, field=thermal_field(nc, L, beta_for(nc), sweeps=1))
+    U = to_np(lat.export())
+    np.testing.assert_allclose(to_np(lat.plaquette()), O.plaquette(U, nc, L), rtol=1e-13, atol=1e-15)
