@@ -22,19 +22,8 @@ struct OpsWide {
         wide::k_init<T><<<4 * c.g.V, wide::kLanes, wide::fp64_lds(c.nc, 2), c.stream>>>((P*)c.links, c.g, c.nc, hot, k0,
                                                                                         k1);
     }
-    static int reunit(const Ctx& c, double* partial) {
-        const size_t lds = wide::fp64_lds(c.nc, 1) + (size_t)c.nc * sizeof(double2);  // M and the projections
-        if (partial)
-            wide::k_reunit<T, true><<<4 * c.g.V, wide::kLanes, lds, c.stream>>>((P*)c.links, c.g, c.nc, partial);
-        else
-            wide::k_reunit<T, false><<<4 * c.g.V, wide::kLanes, lds, c.stream>>>((P*)c.links, c.g, c.nc, nullptr);
-        return 4 * c.g.V;
-    }
-    static int unitarity(const Ctx& c, double* partial) {
-        wide::k_unitarity<T><<<4 * c.g.V, wide::kLanes, wide::fp64_lds(c.nc, 1), c.stream>>>((const P*)c.links, c.g,
-                                                                                             c.nc, partial);
-        return 4 * c.g.V;
-    }
+    static int reunit(const Ctx& c, double* partial) { return launch_reunit_wide<T>(c, partial); }
+    static int unitarity(const Ctx& c, double* partial) { return launch_unitarity_wide<T>(c, partial); }
     static int plaquette(const Ctx& c, double* partial) {
         launch_plaquette_wide<T>(c, partial);
         return c.g.V;
@@ -66,8 +55,7 @@ struct OpsWide {
             launch_update_large_batch<T>(d, n, tiles, hb, mu, par, off, nc, s);
     }
     static void reunit_batch(const ChainDesc* d, int n, int tiles, int nc, hipStream_t s) {
-        wide::k_reunit_batch<T><<<tiles, wide::kLanes, wide::fp64_lds(nc, 1) + (size_t)nc * sizeof(double2), s>>>(
-            d, n, nc);
+        launch_reunit_wide_batch<T>(d, n, tiles, nc, s);
     }
     static void plaquette_batch(const ChainDesc* d, int n, int tiles, double* out, int nc, hipStream_t s) {
         launch_plaquette_wide_batch<T>(d, n, tiles, nc, s);

@@ -532,10 +532,10 @@ int upload_table(sun_batch_t b) {
         for (int i = gr.first; i < gr.first + gr.count; ++i) {
             sun::ChainDesc& c = b->host[i];
             for (int k = 0; k < 5; ++k) c.tile0[k] = t[k];
-            if (gr.wide) {  // one workgroup per updated link and site (or few of them), per link
+            if (gr.wide) {  // one workgroup per updated link, site and link, or few of them
                 t[sun::TILE_HALF_HB] += sun::wide_update_tiles(gr.nc, c.g.Vh);
                 t[sun::TILE_SITE] += sun::wide_plaquette_tiles(gr.nc, c.g.V);
-                t[sun::TILE_LINK] += 4 * c.g.V;
+                t[sun::TILE_LINK] += sun::wide_reunit_tiles(gr.nc, c.g.V);
                 t[sun::TILE_SPATIAL] += c.g.V / c.g.L[3];
                 t[sun::TILE_HALF_OR] += sun::wide_update_tiles(gr.nc, c.g.Vh);
                 continue;

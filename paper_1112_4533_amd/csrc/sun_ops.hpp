@@ -153,6 +153,17 @@ inline int wide_update_tiles(int nc, int Vh) {
 inline int wide_plaquette_tiles(int nc, int V) {
     return nc <= kWideSmallMax ? (V + kWideSmallLinks - 1) / kWideSmallLinks : V;
 }
+// Re-unitarization: a wavefront takes four links up to Nc = 8, two up to 16.
+inline int wide_reunit_tiles(int nc, int V) {
+    const int links = nc <= 8 ? 4 : nc <= 16 ? 2 : 1;
+    return (4 * V + links - 1) / links;
+}
+template <typename T>
+int launch_reunit_wide(const Ctx& c, double* partial);
+template <typename T>
+int launch_unitarity_wide(const Ctx& c, double* partial);
+template <typename T>
+void launch_reunit_wide_batch(const ChainDesc* d, int n, int tiles, int nc, hipStream_t s);
 template <typename T>
 void launch_plaquette_wide(const Ctx& c, double* partial);
 template <typename T>

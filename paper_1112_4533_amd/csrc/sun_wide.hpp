@@ -493,23 +493,6 @@ __device__ __forceinline__ void lds_det(double2* D, int n, double& dr, double& d
     }
 }
 
-// max_ij |(M^dag M - 1)_ij| (M unchanged).
-__device__ __forceinline__ double lds_unitarity_dev(const double2* M, int n) {
-    const int n2 = n * n;
-    double du2 = 0.0;
-    for (int e = threadIdx.x; e < n2; e += kLanes) {
-        const int i = e / n, j = e - i * n;
-        if (j < i) continue;  // Hermitian: the upper triangle has every modulus
-        double r = (i == j) ? -1.0 : 0.0, m = 0.0;
-        for (int k = 0; k < n; ++k) {
-            const double2 a = M[k * n + i], b = M[k * n + j];
-            cmac(r, m, a.x, -a.y, b.x, b.y);
-        }
-        du2 = fmax(du2, nan_to_inf(fmadd(m, m, r * r)));  // a NaN entry counts as infinite
-    }
-    return sqrt(wave_max(du2));
-}
-
 // Gram-Schmidt on all rows, then the last row times conj(det)/|det| (paper
 // Sec. 2, re-unitarization; Nc > 3).  Each row is orthogonalized against the
 // earlier ones by classical Gram-Schmidt, with a second pass where the
@@ -619,81 +602,6 @@ __device__ __forceinline__ void link_id(const Geom& g, int id, int& mu, int& par
     const int rem = id - mu * g.V;
     par = rem >= g.Vh ? 1 : 0;
     h = rem - par * g.Vh;
-}
-
-// Re-unitarization of link blockIdx.x; with REPORT the deviation found before
-// the projection goes to partial[2 id], [2 id + 1].  LDS: one FP64 matrix M
-// and the n projections P.  The link is read twice: once for det M (the LU
-// elimination destroys its copy), once for the Gram-Schmidt.
-template <typename T, bool REPORT>
-__device__ __forceinline__ void reunit_link_wide(T2<T>* __restrict__ U, const Geom& g, int n, int id,
-                                                 double* __restrict__ partial) {
-    extern __shared__ double4 smem_reunit[];
-    const int n2 = n * n;
-    double2* M = reinterpret_cast<double2*>(smem_reunit);
-    double2* P = M + n2;
-    int mu, par, h;
-    link_id(g, id, mu, par, h);
-    double du = 0.0, dd = 0.0;
-    if ((g.present >> mu) & 1) {
-        const T2<T>* src = link_at<T>(U, n2, mu, par, h, g.Vh);
-        lds_load<double, T>(M, src, n);
-        __syncthreads();
-        if (REPORT) du = lds_unitarity_dev(M, n);
-        __syncthreads();
-        double dr, di;
-        lds_det(M, n, dr, di);
-        if (REPORT) dd = nan_to_inf(sqrt(fmadd(di, di, (dr - 1.0) * (dr - 1.0))));
-        __syncthreads();
-        lds_load<double, T>(M, src, n);
-        __syncthreads();
-        lds_reunit(M, P, n, dr, di);
-        T2<T>* dst = const_cast<T2<T>*>(src);
-        for (int e = threadIdx.x; e < n2; e += kLanes) dst[e] = cpx<T>((T)M[e].x, (T)M[e].y);
-    }
-    if (REPORT && threadIdx.x == 0) {
-        partial[2 * (size_t)id] = du;
-        partial[2 * (size_t)id + 1] = dd;
-    }
-}
-
-template <typename T, bool REPORT>
-__global__ __launch_bounds__(kLanes) void k_reunit(T2<T>* __restrict__ U, Geom g, int n,
-                                                   double* __restrict__ partial) {
-    reunit_link_wide<T, REPORT>(U, g, n, (int)blockIdx.x, partial);
-}
-
-// Re-unitarization of every chain of a batch group: one workgroup per link
-// (TILE_LINK counts links here).
-template <typename T>
-__global__ __launch_bounds__(kLanes) void k_reunit_batch(const ChainDesc* __restrict__ d, int nchains, int n) {
-    const int c = find_chain<TILE_LINK>(d, nchains, (int)blockIdx.x);
-    reunit_link_wide<T, false>((T2<T>*)d[c].links, d[c].g, n, (int)blockIdx.x - d[c].tile0[TILE_LINK], nullptr);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kLanes) void k_unitarity(const T2<T>* __restrict__ U, Geom g, int n,
-                                                      double* __restrict__ partial) {
-    extern __shared__ double4 smem_unit[];
-    const int n2 = n * n;
-    double2* M = reinterpret_cast<double2*>(smem_unit);
-    const int id = blockIdx.x;
-    int mu, par, h;
-    link_id(g, id, mu, par, h);
-    double du = 0.0, dd = 0.0;
-    if ((g.present >> mu) & 1) {
-        lds_load<double, T>(M, link_at<T>(U, n2, mu, par, h, g.Vh), n);
-        __syncthreads();
-        du = lds_unitarity_dev(M, n);
-        __syncthreads();
-        double dr, di;
-        lds_det(M, n, dr, di);
-        dd = nan_to_inf(sqrt(fmadd(di, di, (dr - 1.0) * (dr - 1.0))));
-    }
-    if (threadIdx.x == 0) {
-        partial[2 * (size_t)id] = du;
-        partial[2 * (size_t)id + 1] = dd;
-    }
 }
 
 // Start configuration of link blockIdx.x: identity, or a Haar draw (Gaussian

@@ -408,3 +408,25 @@ def test_wide_plaquette_of_every_tile_form(gpu, nc, dtype, L):
     lat = gpu_lattice(gpu, nc, L, dtype, field=thermal_field(nc, L, beta_for(nc), sweeps=1))
     U = to_np(lat.export())
     np.testing.assert_allclose(to_np(lat.plaquette()), O.plaquette(U, nc, L), rtol=1e-13, atol=1e-15)
+
+
+@pytest.mark.parametrize("nc,noise", [(5, 1e-3), (6, 1e-3), (7, 1e-3), (8, 1e-3), (12, 1e-3), (13, 1e-3), (17, 1e-3),
+                                      (24, 1e-3), (25, 1e-3), (6, 1.0), (8, 1.0), (13, 1.0), (25, 1.0)])
+def test_wide_reunitarize_row_layouts(gpu, nc, noise):
+    """Re-unitarization at the first and last Nc of each row layout (8, 16 or
+    32 lanes a row), near-unitary links and general ones (second pass), with
+    the deviations found before; and the same bits without the report.  The
+    tolerances are those of test_wide_reunitarize_parity."""
+    L = (2, 2, 2, 2)
+    rng = np.random.default_rng(100 + nc)
+    U = O.new_field(nc, L, hot=True, seed=19)
+    U = U + noise * (rng.standard_normal(U.shape) + 1j * rng.standard_normal(U.shape))
+    lat, plain = (gpu_lattice(gpu, nc, L, "f64w", field=U) for _ in range(2))
+    before = to_np(lat.reunitarize(report=True))
+    plain.reunitarize()
+    after = to_np(lat.export())
+    assert torch.equal(lat.links, plain.links)
+    np.testing.assert_allclose(before, O.unitarity(U, nc, L), rtol=1e-10)
+    O.reunitarize(U, nc, L)
+    assert np.abs(after - U).max() < (1e-12 if noise < 1 else 1e-10)
+    assert to_np(lat.unitarity()).max() < 1e-13
