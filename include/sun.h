@@ -205,7 +205,10 @@ int sun_set_step(sun_lattice_t h, uint64_t step);
  * runs, and sun_get_launch reports the walk in effect (0 for linear).
  * Defaults: heatbath (256, 1, 16, 4); overrelaxation (256, 1, 12, 4) for
  * links of at most 48 bytes, (256, 1, 8, 4) for larger ones.  A tuning
- * choice only: results are bitwise the same for every shape. */
+ * choice only: results are bitwise the same for every shape.  The phases of a
+ * small lattice (at most 32768 links per direction and parity of SU(2), 16384
+ * of SU(3), 20480 of SU(4)) have one shape of their own, four work-items to a
+ * link: for them it is kept and reported, and changes nothing. */
 int sun_set_launch(sun_lattice_t h, int kind, int block, int xcd, int waves, int tblock);
 int sun_get_launch(sun_lattice_t h, int kind, int *block, int *xcd, int *waves, int *tblock);
 

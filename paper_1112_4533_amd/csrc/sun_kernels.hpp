@@ -214,10 +214,10 @@ __device__ __forceinline__ Quat<T> staple_su2(const T2<T>* __restrict__ U, const
     return A;
 }
 
-// Normalised subgroup direction V = P / |P| (identity when P = 0); returns k.
+// Normalised subgroup direction V = P / |P| (identity when P = 0), k2 = |P|^2;
+// returns k.
 template <typename T>
-__device__ __forceinline__ T unit_quat(const Quat<T>& p, Quat<T>& v) {
-    const T k2 = p.q[0] * p.q[0] + p.q[1] * p.q[1] + p.q[2] * p.q[2] + p.q[3] * p.q[3];
+__device__ __forceinline__ T unit_quat(const Quat<T>& p, T k2, Quat<T>& v) {
     if constexpr (sizeof(T) == 4) {
         // FP32: the hardware reciprocal square root (about 1 ulp)
         if (k2 >= 1.17549435e-38f) {
@@ -236,6 +236,10 @@ __device__ __forceinline__ T unit_quat(const Quat<T>& p, Quat<T>& v) {
         v = Quat<T>{{T(1), T(0), T(0), T(0)}};
     }
     return k;
+}
+template <typename T>
+__device__ __forceinline__ T unit_quat(const Quat<T>& p, Quat<T>& v) {
+    return unit_quat(p, p.q[0] * p.q[0] + p.q[1] * p.q[1] + p.q[2] * p.q[2] + p.q[3] * p.q[3], v);
 }
 
 // ---------------------------------------------------------------------------

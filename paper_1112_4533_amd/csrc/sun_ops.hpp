@@ -143,6 +143,27 @@ const Ops* ops_nc4(int f64);
 const Ops* ops_nc3_two_row(int f64);  // SU(3), rows 0 and 1 stored
 const Ops* ops_wide(int f64);         // 4 <= Nc <= 32: one workgroup per link, link-major storage
 
+// Phases of small lattices take four lanes to a link, kQuadLinks links to a
+// wavefront (sun_quad.hpp).  They win while a phase is about one wavefront per
+// SIMD (1024 of them): beyond it the quad's shared work is issued in turn with
+// other links' and costs more than it shortens.  Overrelaxation / heatbath
+// phase, one lane to a link -> four, in microseconds:
+//   SU(2), two wavefronts per SIMD: FP64 8^4 4.6/9.2 -> 2.9/4.7, 16^4 (at the
+//     limit) 5.2/9.4 -> 4.8/7.6, FP32 16^4 4.7/6.3 -> 4.2/5.1
+//   SU(3), one: FP32 8^4 9.0/11.6 -> 4.5/6.4, 12^4 9.8/12.4 -> 6.6/8.4;
+//     FP64 12 12 14 16 (at the limit) 11.0/19.3 -> 9.2/14.8, 14^4 (past it)
+//     11.4/19.6 -> 12.4/19.8
+//   SU(4), five quarters: 12^4 FP32 17.8/21.9 -> 10.9/14.7, FP64 20.9/58.1 ->
+//     12.1/24.5; 14^4 18.4/22.7 -> 13.9/18.6; 14^3 16 (past it) FP32 18.3/22.7 ->
+//     17.8/22.1, FP64 22.4/60.2 -> 23.9/48.1
+constexpr int kQuadLinks = 16;
+template <int N>
+inline bool quad_applies(const Geom& g) {
+    return g.Vh <= kQuadLinks * (N == 2 ? 2048 : N == 3 ? 1024 : 1280);
+}
+template <int N, typename T, int R>
+void launch_update_quad(const Ctx& c, int kind, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step);
+
 // Up to Nc = kWideSmallMax an update workgroup (one wavefront) takes
 // kWideSmallLinks links, above it (two wavefronts) one.
 constexpr int kWideSmallMax = 8, kWideSmallLinks = 4;

@@ -89,6 +89,10 @@ struct OpsImpl {
 
     static void update(const Ctx& c, int kind, int mu, int par, double beta, uint32_t k0, uint32_t k1,
                        uint32_t step) {
+        if (quad_applies<N>(c.g)) {
+            launch_update_quad<N, T, R>(c, kind, mu, par, beta, k0, k1, step);
+            return;
+        }
         if (kind == 0)
             update_kind<true>(c, mu, par, (T)beta, k0, k1, step);
         else

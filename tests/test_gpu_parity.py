@@ -725,6 +725,43 @@ def test_every_launch_shape_gives_the_same_bits(gpu, nc, dtype):
             assert torch.equal(ref, lat.links), (shape, spt)
 
 
+@pytest.mark.parametrize("nc,dtype,L,beta", [
+    (2, "f32", (2, 2, 2, 2), 2.3), (2, "f64", (16, 16, 16, 16), 2.3), (2, "f64", (6, 1, 4, 10), 0.05),
+    (3, "f32", (2, 2, 2, 2), 6.0), (3, "f32", (6, 1, 1, 2), 6.0), (3, "f32r12", (8, 16, 16, 16), 6.0),
+    (3, "f32r12", (6, 10, 2, 6), 0.05), (3, "f64", (8, 16, 16, 16), 6.0), (3, "f64r12", (2, 6, 1, 10), 6.0),
+    (4, "f32", (2, 2, 2, 2), 11.1), (4, "f32", (10, 16, 16, 16), 0.05), (4, "f64", (6, 2, 10, 1), 11.1)])
+def test_small_lattice_phases_give_the_bits_of_the_batched_ones(gpu, nc, dtype, L, beta):
+    """A small lattice's phases share a link among four lanes; a batch's give
+    it to one.  Every link, from fewer than one workgroup's to the largest
+    lattice of that form, with absent directions and with couplings that reject
+    most first attempts, has the same bits."""
+    sun = gpu
+    a, b = (gpu_lattice(sun, nc, L, dtype, hot=True, seed=8) for _ in range(2))
+    bt = sun.Batch([b], [beta], [5])
+    for _ in range(2):
+        a.sweep(beta, 2, 2, seed=5)
+        bt.sweep(2, 2)
+    torch.cuda.synchronize()
+    assert torch.equal(a.links, b.links)
+
+
+@pytest.mark.parametrize("nc,dtype,L", [(2, "f32", (16, 16, 16, 18)), (3, "f32", (16, 16, 8, 18)),
+                                         (3, "f64", (16, 16, 8, 18)), (4, "f32", (16, 16, 12, 16))])
+def test_launch_shapes_past_the_small_lattices(gpu, nc, dtype, L):
+    """The one-lane phases just past the size that takes four lanes to a link:
+    every workgroup size, walk and number of sites gives the same bits."""
+    sun = gpu
+    ref = gpu_lattice(sun, nc, L, dtype, hot=True, seed=8)
+    ref.sweep(BETA[nc], 1, 2, seed=8)
+    for shape, spt in [((64, 1, 0, 0), 1), ((128, 0, 12, 2), 1), ((64, 0, 8, 2), 2), ((256, 1, 16, 0), 4)]:
+        lat = gpu_lattice(sun, nc, L, dtype, hot=True, seed=8)
+        lat.set_launch(*shape)
+        lat.set_sites_per_item(spt)
+        lat.sweep(BETA[nc], 1, 2, seed=8)
+        torch.cuda.synchronize()
+        assert torch.equal(ref.links, lat.links), (shape, spt)
+
+
 @pytest.mark.parametrize("nc,dtype,L", [(3, "f32r12", (16, 16, 4, 8)), (3, "f64", (6, 4, 2, 6)),
                                          (2, "f32", (8, 8, 8, 8)), (4, "f32", (4, 4, 4, 4))])
 def test_random_tile_orders_give_the_same_bits(gpu, nc, dtype, L):
