@@ -204,7 +204,9 @@ int sun_set_step(sun_lattice_t h, uint64_t step);
  * workgroups (L_x L_y / 2 a multiple of block); elsewhere the linear walk
  * runs, and sun_get_launch reports the walk in effect (0 for linear).
  * Defaults: heatbath (256, 1, 16, 4); overrelaxation (256, 1, 12, 4) for
- * links of at most 48 bytes, (256, 1, 8, 4) for larger ones.  A tuning
+ * links of at most 48 bytes, (256, 1, 8, 4) for larger ones; 64-item
+ * workgroups instead, (64, 1, 0, 0) on medium lattices and (64, 1, 8, 4) for
+ * some phases of large SU(3) ones, where they are faster.  A tuning
  * choice only: results are bitwise the same for every shape.  The phases of a
  * small lattice (at most 32768 links per direction and parity of SU(2), 16384
  * of SU(3), 20480 of SU(4)) have one shape of their own, four work-items to a
@@ -309,9 +311,9 @@ int sun_batch_capture(sun_batch_t b, int n_sweeps, int n_hb, int n_or, int reuni
 int sun_batch_replay(sun_batch_t b, sun_stream_t stream);
 
 /* Launch shape of the batch's register-path phase kernels (as
- * sun_set_launch, always with the linear tile walk; default (256, 1, 0) for
- * both kinds; the workgroup-per-link groups take only its block size, as a
- * single lattice does).  Waits for the
+ * sun_set_launch, always with the linear tile walk; default: 64- or 256-item
+ * workgroups per group of chains of one Nc and storage, by its size and kind,
+ * XCD-aware, no cap; it changes nothing for the workgroup-per-link groups).  Waits for the
  * device, rewrites the table, and drops any captured graph. */
 int sun_batch_set_launch(sun_batch_t b, int kind, int block, int xcd, int waves);
 /* Sites per work-item of the batch's phase kernels (as

@@ -169,11 +169,11 @@ int sun_lattice_create(int nc, const int L[4], int dtype, void* links, size_t li
     h->g = g;
     h->links = links;
     h->link_bytes = link_bytes_of(nc, g, dtype);
-    // Default wave caps, from launch-shape sweeps on SU(3) 32^4: the heatbath
-    // runs best with 16 resident waves per CU whatever the storage; the
-    // overrelaxation kernel with 12 for 48-byte links (FP32 two-row) and 8
-    // for larger ones (18-real FP32: 70.0 -> 67.3 us, FP64: 161 -> 152 us).
-    h->shape[SUN_OVERRELAX].waves = h->link_bytes / (4 * (size_t)g.V) > 48 ? 8 : 12;
+    const size_t one_link = h->link_bytes / (4 * (size_t)g.V);
+    h->shape[SUN_OVERRELAX].waves = one_link > 48 ? 8 : 12;
+    if (!is_wide(nc, dtype) && !sun::quad_applies(nc, g))
+        for (int k = 0; k < 2; ++k)
+            h->shape[k] = sun::default_shape(nc, is_f64(dtype), one_link, g.Vh, k == SUN_HEATBATH);
     // On large lattices the heatbath takes two tiles per workgroup (SU(3)
     // 32^4 sweep: two-row 2.040 -> 2.004 ms, 18 reals 3.156 -> 3.151 ms, FP64
     // two-row 4.378 -> 4.356 ms); where that would leave fewer than 1024
@@ -475,15 +475,15 @@ struct sun_batch_s {
         int tiles[5];          // total tiles per grid kind (see TileKind)
         int nc;
         bool wide;             // workgroup-per-link path: tiles count links / sites, one workgroup each
+        // per update kind: default_shape's workgroup; a batch's chains are
+        // small and mostly cache-resident, so no wave cap (64 chains: 1.10e10 ->
+        // 1.13e10 link updates/s against a 12-wave overrelaxation cap)
+        sun::Shape shape[2] = {sun::Shape{256, 1, 0}, sun::Shape{256, 1, 0}};
     };
     std::vector<sun_lattice_t> chains;  // in the caller's order
     std::vector<Group> groups;
     std::vector<sun::ChainDesc> host;   // host copy of the table
     sun::ChainDesc* table = nullptr;    // device
-    // per update kind; a batch's chains are small and mostly cache-resident,
-    // so no wave cap (the launch-shape tuner's choice for the 64-chain batch:
-    // 1.10e10 -> 1.13e10 link updates/s against a 12-wave overrelaxation cap)
-    sun::Shape shape[2] = {sun::Shape{256, 1, 0}, sun::Shape{256, 1, 0}};
     uint64_t hb_steps_done = 0;         // heatbath steps run since creation (all chains alike)
     std::vector<uint64_t> step0;        // chain step counters at creation
     hipGraph_t graph = nullptr;
@@ -512,12 +512,12 @@ int batch_sweep_launches(sun_batch_t b, int n_hb, int n_or, int reunit, const do
             for (int mu = 0; mu < 4; ++mu)
                 for (int p = 0; p < 2; ++p)
                     gr.ops->update_batch(d, gr.count, gr.tiles[sun::TILE_HALF_HB], SUN_HEATBATH, mu, p, (uint32_t)k,
-                                         b->shape[SUN_HEATBATH], gr.nc, s);
+                                         gr.shape[SUN_HEATBATH], gr.nc, s);
         for (int k = 0; k < n_or; ++k)
             for (int mu = 0; mu < 4; ++mu)
                 for (int p = 0; p < 2; ++p)
                     gr.ops->update_batch(d, gr.count, gr.tiles[sun::TILE_HALF_OR], SUN_OVERRELAX, mu, p, 0,
-                                         b->shape[SUN_OVERRELAX], gr.nc, s);
+                                         gr.shape[SUN_OVERRELAX], gr.nc, s);
         if (reunit) gr.ops->reunit_batch(d, gr.count, gr.tiles[sun::TILE_LINK], gr.nc, s);
     }
     if (n_hb > 0) sun::launch_advance_steps(b->table, (int)b->chains.size(), n_hb, s);
@@ -540,11 +540,11 @@ int upload_table(sun_batch_t b) {
                 t[sun::TILE_HALF_OR] += sun::wide_update_tiles(gr.nc, c.g.Vh);
                 continue;
             }
-            t[sun::TILE_HALF_HB] += sun::half_blocks(c.g, b->shape[SUN_HEATBATH].block);
+            t[sun::TILE_HALF_HB] += sun::half_blocks(c.g, gr.shape[SUN_HEATBATH].block);
             t[sun::TILE_SITE] += sun::plaquette_tiles(c.g);
             t[sun::TILE_LINK] += sun::link_blocks(c.g);
             t[sun::TILE_SPATIAL] += sun::spatial_blocks(c.g);
-            t[sun::TILE_HALF_OR] += sun::half_blocks(c.g, b->shape[SUN_OVERRELAX].block);
+            t[sun::TILE_HALF_OR] += sun::half_blocks(c.g, gr.shape[SUN_OVERRELAX].block);
         }
         for (int k = 0; k < 5; ++k) gr.tiles[k] = t[k];
     }
@@ -570,8 +570,9 @@ int batch_reshape(sun_batch_t b, int kind, F apply) {
     for (size_t i = 0; i < b->host.size(); ++i)
         b->host[i].step = b->step0[b->host[i].out_index] + b->hb_steps_done;
     if (int rc = hip_check(hipDeviceSynchronize(), "hipDeviceSynchronize")) return rc;
-    for (int k = 0; k < 2; ++k)
-        if (kind < 0 || kind == k) apply(b->shape[k]);
+    for (auto& gr : b->groups)
+        for (int k = 0; k < 2; ++k)
+            if (kind < 0 || kind == k) apply(gr.shape[k]);
     if (b->exec) {
         (void)hipGraphExecDestroy(b->exec);
         b->exec = nullptr;
@@ -662,7 +663,16 @@ int sun_batch_create(int n, const sun_lattice_t* chains, const double* betas, co
             b->host.push_back(c);
             ++gr.count;
         }
-        if (gr.count) b->groups.push_back(gr);
+        if (!gr.count) continue;
+        if (!gr.wide) {
+            long long links = 0;
+            for (int i = gr.first; i < gr.first + gr.count; ++i) links += b->host[i].g.Vh;
+            const sun_lattice_t h = chains[b->host[gr.first].out_index];
+            for (int k = 0; k < 2; ++k)
+                gr.shape[k].block = sun::default_shape(nc, is_f64(dt), h->link_bytes / (4 * (size_t)h->g.V), links,
+                                                       k == SUN_HEATBATH).block;
+        }
+        b->groups.push_back(gr);
     }
     for (int i = 0; i < n; ++i) b->step0.push_back(chains[i]->step);
     if (int rc = upload_table(b)) {

@@ -186,6 +186,132 @@ __device__ __forceinline__ Mat<N, T> staple(const T2<T>* __restrict__ U, const G
     return A;
 }
 
+// The staple with its loads issued ahead.  Written direction by direction as
+// above, the compiler issues the loads of a direction in two rounds behind its
+// branch, so a work-item waits out seven memory latencies; where a SIMD holds
+// one or two wavefronts that is half of the phase.  Here the six staple terms
+// form a pipeline: the three links of term u + 1 are requested before term u is
+// multiplied out.  The same operations in the same order.  (Two terms ahead:
+// no faster, 16^4 SU(3) FP32 8.5 us both; SU(4), whose term is 96 registers in
+// FP32: 16^4 16.3 us with and without.)
+
+// A link as loaded.
+template <int N, typename T, int R>
+struct Raw {
+    T2<T> e[R * N];
+};
+template <int N, typename T, int R>
+__device__ __forceinline__ Mat<N, T> raw_mat(const Raw<N, T, R>& r) {
+    Mat<N, T> m;
+SUN_MAT_UNROLL
+    for (int e = 0; e < R * N; ++e) {
+        m.re[e / N][e % N] = r.e[e].x;
+        m.im[e / N][e % N] = r.e[e].y;
+    }
+    if constexpr (R < N) third_row(m);
+    return m;
+}
+// its first E entries
+template <int E, int N, typename T, int R>
+__device__ __forceinline__ void load_raw(Raw<N, T, R>& r, const T2<T>* base, int mu, int par, int h, int Vh) {
+    const T2<T>* p = plane0<N, T, R>(base, mu, par, Vh) + h;
+#pragma unroll
+    for (int e = 0; e < E; ++e) r.e[e] = p[(size_t)e * Vh];
+}
+// the updated link itself
+template <bool NT, int N, typename T, int R>
+__device__ __forceinline__ void load_own(Raw<N, T, R>& r, const T2<T>* base, int mu, int par, int h, int Vh) {
+    const T2<T>* p = plane0<N, T, R>(base, mu, par, Vh) + h;
+#pragma unroll
+    for (int e = 0; e < R * N; ++e) r.e[e] = NT ? load_stream<T>(p + (size_t)e * Vh) : p[(size_t)e * Vh];
+}
+
+// The links of one staple term; term u = 0 .. 5: direction other_dir(MU, u / 2),
+// upper (even u) or lower.
+template <int N, typename T, int R>
+struct Term {
+    Raw<N, T, R> a, b, c;
+};
+constexpr int other_dir(int mu, int k) { return k < mu ? k : k + 1; }
+
+template <int N, typename T, int R, int MU, int UN>
+__device__ __forceinline__ void load_term(Term<N, T, R>& n, const T2<T>* __restrict__ U, const Geom& g, const Site& x,
+                                          const Site& xp, int par, int h) {
+    constexpr int NU = other_dir(MU, UN / 2);
+    constexpr bool kRebuild = N == 3 && sizeof(T) == 8;  // as in staple_dir
+    const int op = par ^ 1;
+    // requested also where the direction is absent (one address for all lanes):
+    // behind a branch the requests are issued later (16^4: 8.5 -> 8.9 us)
+    const bool p = (g.present >> NU) & 1;
+    auto at = [&](int hh) { return p ? hh : 0; };
+    if constexpr (UN % 2 == 0) {
+        const Site xpn = step_up(g, x, NU);
+        load_raw<kRebuild ? 6 : R * N>(n.a, U, NU, op, at(xp.s >> 1), g.Vh);
+        load_raw<R * N>(n.b, U, MU, op, at(xpn.s >> 1), g.Vh);
+        load_raw<R * N>(n.c, U, NU, par, at(h), g.Vh);
+    } else {
+        const Site xmn = step_down(g, x, NU), xpmn = step_down(g, xp, NU);
+        load_raw<R * N>(n.a, U, MU, op, at(xmn.s >> 1), g.Vh);
+        load_raw<kRebuild && R == N ? 8 : R * N>(n.b, U, NU, par, at(xpmn.s >> 1), g.Vh);
+        load_raw<R * N>(n.c, U, NU, op, at(xmn.s >> 1), g.Vh);
+    }
+}
+
+template <int N, typename T, int R, int MU, int UN>
+__device__ __forceinline__ void add_term(Mat<N, T>& A, const Term<N, T, R>& n, const Geom& g) {
+    constexpr int NU = other_dir(MU, UN / 2);
+    if (!((g.present >> NU) & 1)) return;
+    if constexpr (N == 3 && sizeof(T) == 8) {
+        // rows 0 and 1 by products, row 2 rebuilt; the left factor's rows 0 and
+        // 1 (upper), the middle one's columns 0 and 1 (lower)
+        const Raw<3, T, R>& part = UN % 2 == 0 ? n.a : n.b;
+        Mat<3, T> p;
+#pragma unroll
+        for (int e = 0; e < 6; ++e) {
+            p.re[e / 3][e % 3] = part.e[e].x;
+            p.im[e / 3][e % 3] = part.e[e].y;
+        }
+        Mat<3, T> s;
+        if constexpr (UN % 2 == 0) {
+            s = mul_nd_rows2(mul_nd_rows2(p, raw_mat<3, T, R>(n.b)), raw_mat<3, T, R>(n.c));
+        } else {
+            if constexpr (R == 3) {
+#pragma unroll
+                for (int e = 6; e < 8; ++e) {
+                    p.re[2][e - 6] = part.e[e].x;
+                    p.im[2][e - 6] = part.e[e].y;
+                }
+            } else {
+                third_row_entry<T>(p, 0);
+                third_row_entry<T>(p, 1);
+            }
+            s = mul_dn_rows2(mul_nn_cols2(raw_mat<3, T, R>(n.a), p), raw_mat<3, T, R>(n.c));
+        }
+        third_row(s);
+        add_to(A, s);
+    } else if constexpr (UN % 2 == 0) {
+        add_mul_nd(A, mul_nd(raw_mat<N, T, R>(n.a), raw_mat<N, T, R>(n.b)), raw_mat<N, T, R>(n.c));
+    } else {
+        add_mul_dn(A, mul_nn(raw_mat<N, T, R>(n.a), raw_mat<N, T, R>(n.b)), raw_mat<N, T, R>(n.c));
+    }
+}
+
+// Terms UN .. 5, the links of term UN already requested; the updated link is
+// requested last.
+template <int N, typename T, int R, int MU, bool NT, int UN = 0>
+__device__ __forceinline__ void staple_terms(Mat<N, T>& A, Raw<N, T, R>& own, Term<N, T, R> (&n)[6],
+                                             const T2<T>* __restrict__ U, const Geom& g, const Site& x,
+                                             const Site& xp, int par, int h) {
+    if constexpr (UN == 0) load_term<N, T, R, MU, 0>(n[0], U, g, x, xp, par, h);
+    if constexpr (UN < 5)
+        load_term<N, T, R, MU, UN + 1>(n[UN + 1], U, g, x, xp, par, h);
+    else
+        load_own<NT>(own, U, MU, par, h, g.Vh);
+    __builtin_amdgcn_sched_barrier(0);
+    add_term<N, T, R, MU, UN>(A, n[UN], g);
+    if constexpr (UN < 5) staple_terms<N, T, R, MU, NT, UN + 1>(A, own, n, U, g, x, xp, par, h);
+}
+
 template <typename T, int MU, int NU>
 __device__ __forceinline__ void staple_dir_su2(Quat<T>& A, const T2<T>* __restrict__ U, const Geom& g, const Site& x,
                                                const Site& xp, int par, int h) {
@@ -248,12 +374,21 @@ __device__ __forceinline__ T unit_quat(const Quat<T>& p, Quat<T>& v) {
 // kept in registers and updated with U.  Shared by the single-lattice and the
 // batched kernels, so a chain gives the same bits either way.
 // ---------------------------------------------------------------------------
-template <int N, typename T, int R, bool HB, int MU, bool NT>
+template <int N, typename T, int R, bool HB, int MU, bool NT, bool AHEAD>
 __device__ __forceinline__ void update_link(T2<T>* __restrict__ U, const Geom& g, int par, int h, T beta,
                                             uint32_t k0, uint32_t k1, uint32_t step) {
     const Site x = site_of(g, par, h);
-    const Mat<N, T> A = staple<N, T, R, MU>(U, g, x, par, h);
-    Mat<N, T> Ul = NT ? load_mat_stream<N, T, R>(U, MU, par, h, g.Vh) : load_mat<N, T, R>(U, MU, par, h, g.Vh);
+    Mat<N, T> A, Ul;
+    if constexpr (AHEAD) {
+        Term<N, T, R> n[6];
+        Raw<N, T, R> own;
+        set_zero(A);
+        staple_terms<N, T, R, MU, NT>(A, own, n, U, g, x, step_up(g, x, MU), par, h);
+        Ul = raw_mat<N, T, R>(own);
+    } else {
+        A = staple<N, T, R, MU>(U, g, x, par, h);
+        Ul = NT ? load_mat_stream<N, T, R>(U, MU, par, h, g.Vh) : load_mat<N, T, R>(U, MU, par, h, g.Vh);
+    }
     Mat<N, T> W = mul_nn(Ul, A);
     const T cb = T(2) * beta / T(N);  // alpha = 2 beta k / N
     int sg = 0;
@@ -312,13 +447,27 @@ __device__ __forceinline__ void update_link_su2(T2<T>* __restrict__ U, const Geo
 // a field that fits keeps it cached for the next phase, which reads it.  A
 // compile-time choice: as a run-time branch it kept the plain loads from
 // being scheduled early.
-template <int N, typename T, int R, bool HB, int MU, bool NT>
+template <int N, typename T, int R, bool HB, int MU, bool NT, bool AHEAD>
 __device__ __forceinline__ void update_any(T2<T>* __restrict__ U, const Geom& g, int par, int h, T beta, uint32_t k0,
                                            uint32_t k1, uint32_t step) {
     if constexpr (N == 2)
         update_link_su2<T, HB, MU, NT>(U, g, par, h, beta, k0, k1, step);
     else
-        update_link<N, T, R, HB, MU, NT>(U, g, par, h, beta, k0, k1, step);
+        update_link<N, T, R, HB, MU, NT, AHEAD>(U, g, par, h, beta, k0, k1, step);
+}
+
+// SU(3) phases in 64-item workgroups issue the staple's loads ahead; where
+// that pays is default_shape's choice of workgroup.  Wavefronts per SIMD that
+// their registers are meant for: two in FP32 (169 to 219 registers), one in
+// FP64 (262 and more; held to two it spills: 24^4 heatbath 68 -> 82 us).
+constexpr bool loads_ahead(int n, int block) { return n == 3 && block == 64; }
+template <int N, typename T>
+constexpr int max_waves(int block) {
+    return !loads_ahead(N, block) ? 8 : sizeof(T) == 4 ? 2 : 1;
+}
+template <int N, typename T>
+constexpr int min_waves(int block) {
+    return loads_ahead(N, block) ? max_waves<N, T>(block) : 1;
 }
 
 // One checkerboard phase of one lattice, BS work-items per workgroup; xcd
@@ -336,13 +485,14 @@ __device__ __forceinline__ void update_any(T2<T>* __restrict__ U, const Geom& g,
 // workgroup takes walk positions blockIdx.x + r gridDim.x, r < walk.spt, in
 // turn (r apart by a multiple of 8 when the grid is, so they stay on one XCD).
 template <int N, typename T, int R, bool HB, int MU, int BS, bool NT>
-__global__ __launch_bounds__(BS) void k_update(T2<T>* __restrict__ U, Geom g, int par, T beta, uint32_t k0,
+__global__ __launch_bounds__(BS)
+    __attribute__((amdgpu_waves_per_eu(min_waves<N, T>(BS), max_waves<N, T>(BS)))) void k_update(T2<T>* __restrict__ U, Geom g, int par, T beta, uint32_t k0,
                                                uint32_t k1, uint32_t step, Walk walk, int nblk) {
     for (int r = 0; r < walk.spt; ++r) {
         const int b = (int)blockIdx.x + r * (int)gridDim.x;
         if (b >= nblk) break;
         const int h = walk_tile(b, nblk, walk) * BS + threadIdx.x;
-        if (h < g.Vh) update_any<N, T, R, HB, MU, NT>(U, g, par, h, beta, k0, k1, step);
+        if (h < g.Vh) update_any<N, T, R, HB, MU, NT, loads_ahead(N, BS)>(U, g, par, h, beta, k0, k1, step);
     }
 }
 
@@ -373,7 +523,8 @@ __device__ __forceinline__ int find_chain(const ChainDesc* __restrict__ d, int n
 // Grid: ceil(tiles / spt) workgroups; workgroup b takes tiles b + r gridDim.x,
 // r < spt, in turn.
 template <int N, typename T, int R, bool HB, int MU, int BS>
-__global__ __launch_bounds__(BS) void k_update_batch(const ChainDesc* __restrict__ d, int n, int par,
+__global__ __launch_bounds__(BS)
+    __attribute__((amdgpu_waves_per_eu(min_waves<N, T>(BS), max_waves<N, T>(BS)))) void k_update_batch(const ChainDesc* __restrict__ d, int n, int par,
                                                      uint32_t step_offset, int xcd, int tiles, int spt) {
     constexpr int KIND = HB ? TILE_HALF_HB : TILE_HALF_OR;
     for (int r = 0; r < spt; ++r) {
@@ -384,8 +535,8 @@ __global__ __launch_bounds__(BS) void k_update_batch(const ChainDesc* __restrict
         const Geom g = d[c].g;
         const int h = (tile - d[c].tile0[KIND]) * BS + threadIdx.x;
         if (h < g.Vh && ((g.present >> MU) & 1))
-            update_any<N, T, R, HB, MU, false>((T2<T>*)d[c].links, g, par, h, (T)d[c].beta, d[c].k0, d[c].k1,
-                                               (uint32_t)(d[c].step + step_offset));
+            update_any<N, T, R, HB, MU, false, loads_ahead(N, BS)>((T2<T>*)d[c].links, g, par, h, (T)d[c].beta, d[c].k0,
+                                                                   d[c].k1, (uint32_t)(d[c].step + step_offset));
     }
 }
 

@@ -746,7 +746,9 @@ def test_small_lattice_phases_give_the_bits_of_the_batched_ones(gpu, nc, dtype, 
 
 
 @pytest.mark.parametrize("nc,dtype,L", [(2, "f32", (16, 16, 16, 18)), (3, "f32", (16, 16, 8, 18)),
-                                         (3, "f64", (16, 16, 8, 18)), (4, "f32", (16, 16, 12, 16))])
+                                         (3, "f64", (16, 16, 8, 18)), (4, "f32", (16, 16, 12, 16)),
+                                         (3, "f32r12", (32, 34, 1, 32)), (3, "f64r12", (34, 2, 16, 32)),
+                                         (3, "f64", (32, 32, 34, 1))])
 def test_launch_shapes_past_the_small_lattices(gpu, nc, dtype, L):
     """The one-lane phases just past the size that takes four lanes to a link:
     every workgroup size, walk and number of sites gives the same bits."""
