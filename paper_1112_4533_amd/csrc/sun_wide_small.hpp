@@ -46,13 +46,21 @@ struct SmallShape {
 };
 
 // LDS of one link: the three factors of a staple term; after the staples W
-// = U A, U, and (heatbath) the draw records of the next subgroup steps.
+// = U A, U, and (heatbath) the draw records of the next subgroup steps.  Its
+// size is half of the banks past their multiple, so that neighbouring links'
+// matrices start in different banks (SU(8) FP64 12^4 sweep step 1239 us at a
+// multiple, 1196 like this).
 template <typename T, int N>
 struct alignas(16) SmallLds {
+    static constexpr int kMatBytes = SmallShape<T, N>::kMat * sizeof(T2<T>);
+    static constexpr int kDrawBytes = SmallShape<T, N>::kChunk * sizeof(DrawRec<T, kQuickHits>);
+    static constexpr int kUsed = 2 * kMatBytes + (kMatBytes > kDrawBytes ? kMatBytes : kDrawBytes);
+    static constexpr int kTail = (kUsed + 127) / 256 * 256 + 128 - 2 * kMatBytes;
     T2<T> q[SmallShape<T, N>::kMat], r[SmallShape<T, N>::kMat];
     union {
         T2<T> left[SmallShape<T, N>::kMat];
-        DrawRec<T> draw[SmallShape<T, N>::kChunk];
+        DrawRec<T, kQuickHits> draw[SmallShape<T, N>::kChunk];
+        char fill[kTail];
     };
 };
 template <typename T, int N>

@@ -399,6 +399,24 @@ def test_wide_two_wavefronts_at_the_edges_of_their_ranges(gpu, nc, dtype):
         compare_links(got, want, dtype, m, k, f"nc={nc} {dtype} kind={kind} beta={beta}", spread=sp, decisions=dec)
 
 
+@pytest.mark.parametrize("nc,dtype", [(6, "f32"), (8, "f64"), (9, "f32"), (22, "f64"), (23, "f64")])
+@pytest.mark.parametrize("scale", [0.02, 0.3])
+def test_wide_heatbath_in_the_creutz_range(gpu, nc, dtype, scale):
+    """Couplings at which most draws are in the Creutz range and many reject
+    their attempts on record (two or three of them), on either side of the
+    Nc from which the FP64 heatbath takes the largest form."""
+    L = (4, 2, 2, 2)
+    base = O.new_field(nc, L, hot=True, seed=67)
+    lat = gpu_lattice(gpu, nc, L, dtype, field=base)
+    lat.phase(0, 2, 1, scale * nc, seed=19, step=3)
+    got = to_np(lat.export())
+    sp = twin_spread(base, nc, L, 0, 2, 1, scale * nc, 19, 3, rel=REL[dtype[:3]])
+    want = base.copy()
+    m, k = oracle_phase_diag(want, nc, L, 0, 2, 1, scale * nc, 19, 3)
+    compare_links(got, want, dtype, m, k, f"nc={nc} {dtype} creutz", spread=sp,
+                  decisions=(np.prod(L) // 2) * nc * (nc - 1) // 2)
+
+
 @pytest.mark.parametrize("nc,dtype,L", [(5, "f32", (6, 2, 1, 2)), (6, "f64", (2, 2, 2, 2)), (7, "f32", (4, 2, 2, 2)),
                                         (8, "f64", (6, 2, 1, 1)), (12, "f32", (4, 2, 2, 2)), (17, "f64", (2, 2, 2, 2)),
                                         (20, "f32", (2, 2, 2, 2)), (25, "f64", (2, 2, 1, 2)), (31, "f32", (2, 2, 2, 2))])
