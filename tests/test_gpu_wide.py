@@ -448,3 +448,30 @@ def test_wide_reunitarize_row_layouts(gpu, nc, noise):
     O.reunitarize(U, nc, L)
     assert np.abs(after - U).max() < (1e-12 if noise < 1 else 1e-10)
     assert to_np(lat.unitarity()).max() < 1e-13
+
+
+@pytest.mark.parametrize("nc,dtype", [(4, "f64w"), (5, "f32"), (6, "f64"), (8, "f32"), (12, "f64"), (13, "f32"),
+                                      (16, "f64"), (25, "f32"), (32, "f64")])
+def test_wide_singular_links_have_determinant_zero(gpu, nc, dtype):
+    """A link that is exactly singular -- all zero, or with a zero first, middle
+    or last column -- has det U = 0, so both deviations are exactly 1 as the
+    oracle's are, wherever the link stands among those of its wavefront; and
+    re-unitarization gives every other link the bits it has without it."""
+    L = (2, 2, 2, 2)
+    base = O.new_field(nc, L, hot=True, seed=23)
+    good = gpu_lattice(gpu, nc, L, dtype, field=base)
+    good.reunitarize()
+    want = to_np(good.export())
+    cols = {"zero": slice(None), "first": 0, "middle": nc // 2, "last": nc - 1}
+    for k, (what, col) in enumerate(cols.items()):
+        mu, s = k, (1, 6, 11, 15)[k]
+        U = base.copy()
+        U[mu, s][:, col] = 0.0
+        lat = gpu_lattice(gpu, nc, L, dtype, field=U)
+        np.testing.assert_allclose(to_np(lat.unitarity()), [1.0, 1.0], rtol=1e-5 if dtype == "f32" else 1e-13)
+        np.testing.assert_allclose(O.unitarity(U, nc, L), [1.0, 1.0], rtol=1e-13)
+        rep = to_np(lat.reunitarize(report=True))
+        np.testing.assert_allclose(rep, [1.0, 1.0], rtol=1e-5 if dtype == "f32" else 1e-13, err_msg=what)
+        got, ref = to_np(lat.export()), want.copy()
+        got[mu, s] = ref[mu, s] = 0.0
+        assert np.array_equal(got, ref), what
