@@ -209,8 +209,9 @@ int sun_set_step(sun_lattice_t h, uint64_t step);
  * some phases of large SU(3) ones, where they are faster.  A tuning
  * choice only: results are bitwise the same for every shape.  The phases of a
  * small lattice (at most 32768 links per direction and parity of SU(2), 16384
- * of SU(3), 20480 of SU(4)) have one shape of their own, four work-items to a
- * link: for them it is kept and reported, and changes nothing. */
+ * of SU(3), 20480 of SU(4); fewer where directions are absent, the
+ * overrelaxation's above all) have one shape of their own, four work-items to
+ * a link: for them it is kept and reported, and changes nothing. */
 int sun_set_launch(sun_lattice_t h, int kind, int block, int xcd, int waves, int tblock);
 int sun_get_launch(sun_lattice_t h, int kind, int *block, int *xcd, int *waves, int *tblock);
 

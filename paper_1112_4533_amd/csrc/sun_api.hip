@@ -171,9 +171,9 @@ int sun_lattice_create(int nc, const int L[4], int dtype, void* links, size_t li
     h->link_bytes = link_bytes_of(nc, g, dtype);
     const size_t one_link = h->link_bytes / (4 * (size_t)g.V);
     h->shape[SUN_OVERRELAX].waves = one_link > 48 ? 8 : 12;
-    if (!is_wide(nc, dtype) && !sun::quad_applies(nc, g))
-        for (int k = 0; k < 2; ++k)
-            h->shape[k] = sun::default_shape(nc, is_f64(dtype), one_link, g.Vh, k == SUN_HEATBATH);
+    for (int k = 0; k < 2; ++k)
+        if (!is_wide(nc, dtype) && !sun::quad_applies(nc, g, k))
+            h->shape[k] = sun::default_shape(nc, is_f64(dtype), one_link, g.Vh, g.present == 15, k == SUN_HEATBATH);
     // On large lattices the heatbath takes two tiles per workgroup (SU(3)
     // 32^4 sweep: two-row 2.040 -> 2.004 ms, 18 reals 3.156 -> 3.151 ms, FP64
     // two-row 4.378 -> 4.356 ms); where that would leave fewer than 1024
@@ -665,12 +665,15 @@ int sun_batch_create(int n, const sun_lattice_t* chains, const double* betas, co
         }
         if (!gr.count) continue;
         if (!gr.wide) {
-            long long links = 0;
-            for (int i = gr.first; i < gr.first + gr.count; ++i) links += b->host[i].g.Vh;
+            long long links = 0, in_full = 0;  // the second: of the chains with all four directions
+            for (int i = gr.first; i < gr.first + gr.count; ++i) {
+                links += b->host[i].g.Vh;
+                if (b->host[i].g.present == 15) in_full += b->host[i].g.Vh;
+            }
             const sun_lattice_t h = chains[b->host[gr.first].out_index];
             for (int k = 0; k < 2; ++k)
                 gr.shape[k].block = sun::default_shape(nc, is_f64(dt), h->link_bytes / (4 * (size_t)h->g.V), links,
-                                                       k == SUN_HEATBATH).block;
+                                                       2 * in_full > links, k == SUN_HEATBATH).block;
         }
         b->groups.push_back(gr);
     }

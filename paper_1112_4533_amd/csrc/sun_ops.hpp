@@ -107,8 +107,8 @@ inline int plaquette_wave_cap(size_t field_bytes) {
 constexpr int kPhaseBlocks[3] = {64, 128, 256};
 inline bool valid_phase_block(int b) { return b == 64 || b == 128 || b == 256; }
 
-// Workgroup, wave cap and walk that a phase of `links` links starts with; a
-// tuner or the caller may replace them.  block 256 unless 64-item workgroups
+// Workgroup, wave cap and walk that a phase of `links` links starts with (full:
+// all four directions are present); a tuner or the caller may replace them.  block 256 unless 64-item workgroups
 // do better, which spread a small grid over all CUs and, for SU(3), issue the
 // staple's loads ahead at half the resident wavefronts.  Overrelaxation /
 // heatbath phase, 256 -> 64, in microseconds:
@@ -126,17 +126,21 @@ inline bool valid_phase_block(int b) { return b == 64 || b == 128 || b == 256; }
 //     54.2 -> 59.1)
 //   SU(3) FP64, up to one: 16^4 12.2/20.5 -> 10.5/19.0; overrelaxation at any
 //     size (24^4 51.3 -> 46.1, 32^4 151 -> 137, two-row 32^4 101 -> 92), the
-//     heatbath not (20^4 36.3 -> 38.3).
+//     heatbath not (20^4 36.3 -> 38.3)
+//   SU(3) with a direction absent: never.  The loads ahead are issued for it
+//     too, and a wavefront of fewer staples does better with others beside it
+//     (256 512 FP32 7.6/12.8 -> 10.7/16.1, 48^3 9.4/12.6 -> 10.8/14.4; FP64
+//     overrelaxation 512^2 17.4 -> 22.3, 56^3 19.5 -> 21.7).
 // Wave caps of larger grids, from sweeps on SU(3) 32^4: the heatbath 16
 // resident waves per CU whatever the storage, the overrelaxation 12 for
 // 48-byte links (FP32 two-row) and 8 for larger ones (18-real FP32 70.0 -> 67.3
 // us, FP64 161 -> 152); a grid of two wavefronts per SIMD needs none, nor a
 // t-blocked walk (16^4 8.5 -> 8.8 with one).
-inline Shape default_shape(int nc, bool f64, size_t link_bytes, long long links, bool heatbath) {
+inline Shape default_shape(int nc, bool f64, size_t link_bytes, long long links, bool full, bool heatbath) {
     const long long per_simd = 1024 * 64;  // links of one wavefront on every SIMD
     const long long few = nc != 3 ? 2 * per_simd : f64 ? per_simd : per_simd * 3 / 2;
-    if (links <= few) return Shape{64, 1, 0, 0};
-    if (nc == 3) {
+    if (links <= few && (nc != 3 || full)) return Shape{64, 1, 0, 0};
+    if (nc == 3 && full) {
         const bool many = heatbath ? !f64 && link_bytes > 48 && links >= 4 * per_simd : f64 || links >= 6 * per_simd;
         if (many) return Shape{64, 1, 8, 4};
     }
@@ -192,9 +196,24 @@ const Ops* ops_wide(int f64);         // 4 <= Nc <= 32: one workgroup per link, 
 //   SU(4), five quarters: 12^4 FP32 17.8/21.9 -> 10.9/14.7, FP64 20.9/58.1 ->
 //     12.1/24.5; 14^4 18.4/22.7 -> 13.9/18.6; 14^3 16 (past it) FP32 18.3/22.7 ->
 //     17.8/22.1, FP64 22.4/60.2 -> 23.9/48.1
+// With fewer directions a link has fewer staples, a one-lane work-item is
+// sooner done and the overrelaxation's line lies lower:
+//   three directions: SU(2) 32 32 64 (two per SIMD) 4.1/6.2 -> 4.3/5.6, 48 48 20
+//     4.2/6.2 -> 3.9/5.2; SU(3) FP32 32^3 (one) 7.7/10.8 -> 7.6/9.6; SU(4) FP64
+//     32 32 40 (five quarters) 15.5/55 -> 18.8/44, 32^3 15.1/54 -> 13.1/28
+//   two: SU(2) FP64 256^2 (two) 4.1/10.4 -> 4.5/9.2, 192 256 4.0/10.3 -> 4.0/8.6;
+//     SU(3) FP64 128 256 (one) 6.7/18.6 -> 7.9/15.4, 128 160 6.2 -> 6.6, 128^2
+//     (half) 6.1/19.7 -> 5.6/12.9; SU(4) FP32 160 256 (five quarters) 10.1/17.4 ->
+//     13.9/19.1, 128 256 (one) 9.8/17.1 -> 11.6/16.6, 128 192 9.5/17.1 -> 9.6/14.3
+//   one (no staples): SU(3) 16384 4.9/8.2 -> 5.1/7.7, 65536 4.9/8.4 -> 6.1/10.6
 constexpr int kQuadLinks = 16;
-inline bool quad_applies(int nc, const Geom& g) {
-    return g.Vh <= kQuadLinks * (nc == 2 ? 2048 : nc == 3 ? 1024 : 1280);
+// wavefronts: [directions - 1][Nc - 2][heatbath, overrelaxation]
+constexpr int kQuadWaves[4][3][2] = {{{1024, 0}, {512, 0}, {640, 0}},
+                                     {{2048, 1536}, {1024, 512}, {1024, 768}},
+                                     {{2048, 1536}, {1024, 1024}, {1280, 1024}},
+                                     {{2048, 2048}, {1024, 1024}, {1280, 1280}}};
+inline bool quad_applies(int nc, const Geom& g, int kind) {
+    return g.Vh <= kQuadLinks * kQuadWaves[__builtin_popcount(g.present) - 1][nc - 2][kind];
 }
 template <int N, typename T, int R>
 void launch_update_quad(const Ctx& c, int kind, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step);

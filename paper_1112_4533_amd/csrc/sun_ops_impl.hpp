@@ -89,7 +89,7 @@ struct OpsImpl {
 
     static void update(const Ctx& c, int kind, int mu, int par, double beta, uint32_t k0, uint32_t k1,
                        uint32_t step) {
-        if (quad_applies(N, c.g)) {
+        if (quad_applies(N, c.g, kind)) {
             launch_update_quad<N, T, R>(c, kind, mu, par, beta, k0, k1, step);
             return;
         }

@@ -269,8 +269,8 @@ class Lattice:
         """Launch shape of the heatbath (kind 0), overrelaxation (1) or both
         (-1) phase kernels.  Accepted on the workgroup-per-link path (Nc >=
         5, or the WIDE storages) and for small lattices (at most 32768 links
-        per direction and parity of SU(2), 16384 of SU(3), 20480 of SU(4)),
-        where it changes nothing."""
+        per direction and parity of SU(2), 16384 of SU(3), 20480 of SU(4),
+        fewer where directions are absent), where it changes nothing."""
         _check(load().sun_set_launch(self._h, int(kind), int(block), int(xcd), int(waves), int(tblock)))
 
     def get_launch(self, kind):

@@ -147,6 +147,35 @@ def test_create_validates_buffers_without_touching_them(lib):
     lib.sun_lattice_destroy(h)
 
 
+@pytest.mark.parametrize("nc,L,dtype,hb,orx", [
+    # medium and large SU(3) lattices start with 64-item workgroups where all
+    # four directions are present, never with one absent
+    (3, (16, 16, 16, 16), 0, (64, 1, 0, 0), (64, 1, 0, 0)),
+    (3, (32, 32, 32, 32), 1, (256, 1, 16, 4), (64, 1, 8, 4)),
+    (3, (256, 512, 1, 1), 0, (256, 1, 16, 0), (256, 1, 8, 0)),
+    (3, (1024, 1024, 1, 1), 0, (256, 1, 16, 0), (256, 1, 8, 0)),
+    (3, (1024, 1024, 1, 1), 2, (256, 1, 16, 0), (256, 1, 12, 0)),
+    (3, (48, 48, 48, 1), 1, (256, 1, 16, 0), (256, 1, 8, 0)),
+    (3, (128, 2, 16, 64), 3, (256, 1, 16, 0), (64, 1, 8, 4)),
+    (3, (128, 1, 16, 64), 3, (256, 1, 16, 0), (256, 1, 8, 0)),
+    # SU(2) and SU(4), whose loads are not issued ahead, at either
+    (4, (256, 256, 1, 1), 0, (64, 1, 0, 0), (64, 1, 0, 0)),
+    # between the lines of the two kinds: the overrelaxation has a shape that
+    # takes effect, the small heatbath keeps its initial one
+    (4, (128, 256, 1, 1), 0, (256, 1, 16, 0), (64, 1, 0, 0))])
+def test_default_launch_shapes(lib, nc, L, dtype, hb, orx):
+    h = ctypes.c_void_p()
+    rc, lb, sb = _bytes(lib, nc, L, dtype)
+    assert rc == 0
+    assert lib.sun_lattice_create(nc, (ctypes.c_int * 4)(*L), dtype, ctypes.c_void_p(0x10000), lb,
+                                  ctypes.c_void_p(0x20000), sb, ctypes.byref(h)) == 0
+    v = [ctypes.c_int() for _ in range(4)]
+    for kind, want in ((0, hb), (1, orx)):
+        assert lib.sun_get_launch(h, kind, *[ctypes.byref(x) for x in v]) == 0
+        assert tuple(x.value for x in v) == want, kind
+    lib.sun_lattice_destroy(h)
+
+
 def test_batch_argument_checks(lib):
     tb = ctypes.c_size_t()
     assert lib.sun_batch_bytes(0, ctypes.byref(tb)) == -1

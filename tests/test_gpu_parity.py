@@ -745,6 +745,22 @@ def test_small_lattice_phases_give_the_bits_of_the_batched_ones(gpu, nc, dtype, 
     assert torch.equal(a.links, b.links)
 
 
+@pytest.mark.parametrize("nc,dtype,L", [(2, "f64", (256, 256, 1, 1)), (2, "f32", (32, 32, 64, 1)),
+                                         (3, "f32", (128, 160, 1, 1)), (3, "f64", (128, 1, 1, 256)),
+                                         (4, "f32", (128, 256, 1, 1)), (4, "f64", (32, 32, 1, 40)),
+                                         (3, "f32r12", (16384, 1, 1, 1)), (3, "f64r12", (256, 512, 1, 1))])
+def test_fewer_directions_between_the_lines_of_the_kinds(gpu, nc, dtype, L):
+    """Lattices with absent directions where the heatbath has four lanes to a
+    link and the overrelaxation one (the last: one for both)."""
+    sun = gpu
+    a, b = (gpu_lattice(sun, nc, L, dtype, hot=True, seed=8) for _ in range(2))
+    bt = sun.Batch([b], [BETA[nc]], [5])
+    a.sweep(BETA[nc], 1, 2, seed=5)
+    bt.sweep(1, 2)
+    torch.cuda.synchronize()
+    assert torch.equal(a.links, b.links)
+
+
 @pytest.mark.parametrize("nc,dtype,L", [(2, "f32", (16, 16, 16, 18)), (3, "f32", (16, 16, 8, 18)),
                                          (3, "f64", (16, 16, 8, 18)), (4, "f32", (16, 16, 12, 16)),
                                          (3, "f32r12", (32, 34, 1, 32)), (3, "f64r12", (34, 2, 16, 32)),
