@@ -173,7 +173,7 @@ int sun_lattice_create(int nc, const int L[4], int dtype, void* links, size_t li
     h->shape[SUN_OVERRELAX].waves = one_link > 48 ? 8 : 12;
     for (int k = 0; k < 2; ++k)
         if (!is_wide(nc, dtype) && !sun::quad_applies(nc, g, k))
-            h->shape[k] = sun::default_shape(nc, is_f64(dtype), one_link, g.Vh, g.present == 15, k == SUN_HEATBATH);
+            h->shape[k] = sun::default_shape(nc, is_f64(dtype), one_link, sun::phase_grid(g, false), k == SUN_HEATBATH);
     // On large lattices the heatbath takes two tiles per workgroup (SU(3)
     // 32^4 sweep: two-row 2.040 -> 2.004 ms, 18 reals 3.156 -> 3.151 ms, FP64
     // two-row 4.378 -> 4.356 ms); where that would leave fewer than 1024
@@ -665,15 +665,20 @@ int sun_batch_create(int n, const sun_lattice_t* chains, const double* betas, co
         }
         if (!gr.count) continue;
         if (!gr.wide) {
-            long long links = 0, in_full = 0;  // the second: of the chains with all four directions
+            // all the group's links, and those of chains that have all four
+            // directions or large planes: the group goes by most of them
+            long long links = 0, full = 0, far = 0;
             for (int i = gr.first; i < gr.first + gr.count; ++i) {
-                links += b->host[i].g.Vh;
-                if (b->host[i].g.present == 15) in_full += b->host[i].g.Vh;
+                const sun::PhaseGrid p = sun::phase_grid(b->host[i].g, true);
+                links += p.links;
+                if (p.full) full += p.links;
+                if (p.far) far += p.links;
             }
             const sun_lattice_t h = chains[b->host[gr.first].out_index];
             for (int k = 0; k < 2; ++k)
-                gr.shape[k].block = sun::default_shape(nc, is_f64(dt), h->link_bytes / (4 * (size_t)h->g.V), links,
-                                                       2 * in_full > links, k == SUN_HEATBATH).block;
+                gr.shape[k].block = sun::default_shape(nc, is_f64(dt), h->link_bytes / (4 * (size_t)h->g.V),
+                                                       sun::PhaseGrid{links, 2 * full > links, 2 * far > links},
+                                                       k == SUN_HEATBATH).block;
         }
         b->groups.push_back(gr);
     }

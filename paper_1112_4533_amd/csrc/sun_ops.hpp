@@ -107,11 +107,22 @@ inline int plaquette_wave_cap(size_t field_bytes) {
 constexpr int kPhaseBlocks[3] = {64, 128, 256};
 inline bool valid_phase_block(int b) { return b == 64 || b == 128 || b == 256; }
 
-// Workgroup, wave cap and walk that a phase of `links` links starts with (full:
-// all four directions are present); a tuner or the caller may replace them.  block 256 unless 64-item workgroups
-// do better, which spread a small grid over all CUs and, for SU(3), issue the
-// staple's loads ahead at half the resident wavefronts.  Overrelaxation /
-// heatbath phase, 256 -> 64, in microseconds:
+// What a phase's default launch shape follows from besides the link type.
+struct PhaseGrid {
+    long long links;  // links a phase updates
+    bool full;        // all four directions present
+    bool far;         // 64-item workgroups would walk linearly over large planes
+};
+inline PhaseGrid phase_grid(const Geom& g, bool linear) {  // linear: the walk is never t-blocked (a batch's)
+    const int plane = g.L[0] * g.L[1] / 2;
+    return PhaseGrid{g.Vh, g.present == 15, plane > 12 * 64 && (linear || plane % 64 != 0 || g.L[3] % 4 != 0)};
+}
+
+// Workgroup, wave cap and walk that a phase starts with; a tuner or the caller
+// may replace them.  block 256 unless 64-item workgroups do better, which
+// spread a small grid over all CUs and, for SU(3), issue the staple's loads
+// ahead at half the resident wavefronts.  Overrelaxation / heatbath phase,
+// 256 -> 64, in microseconds:
 //   SU(2), SU(4), up to two wavefronts per SIMD: SU(2) FP32 20^4 6.0/7.3 ->
 //     5.3/7.0, SU(4) 16^4 FP32 18.6/23.0 -> 16.4/21.6, FP64 24.7/61.8 -> 23.4/53.9;
 //     past it equal (SU(4) 24^4 54.3/60.7, 55.0/59.9) or slower (SU(2) 32^4
@@ -119,13 +130,17 @@ inline bool valid_phase_block(int b) { return b == 64 || b == 128 || b == 256; }
 //   SU(3) FP32, up to one and a half: 16^4 10.9/13.7 -> 8.5/11.7, 20^4 16.3/19.6 ->
 //     13.6/17.6; slower past it (16 32 16 32 20.1/23.4 -> 21.1/24.0, 24^4
 //     26.9/29.9 -> 28.0/31.1), until the caches no longer hold the field and fewer
-//     wavefronts re-read more from L2: overrelaxation from six per SIMD on
-//     (28^4 45.4 -> 47.2, 20 20 48 48 66.7 -> 66.4, 32^4 73.3 -> 71.4,
-//     16 32 48 48 96.5 -> 88.1), heatbath of 72-byte links from four on
-//     (16 32 32 32 44.4 -> 40.1, 32^4 88.0 -> 78.0), of 48-byte ones not (32^4
-//     54.2 -> 59.1)
+//     wavefronts re-read more from L2: overrelaxation of 72-byte links from eight
+//     per SIMD on (28^4 45.4 -> 47.2, 24 24 40 38 62.7 -> 64.9, 24 24 40 44 74.4 ->
+//     76.0, 32^4 73.5 -> 71.7, 16 32 48 48 97.2 -> 88.2, 48^4 531 -> 436), of
+//     48-byte ones from six (24 24 40 36 45.9 -> 46.0, 20 20 48 48 45.2 -> 44.0,
+//     32^4 48.2 -> 46.8, 36^4 89.6 -> 84.8, 48^4 310 -> 289); heatbath of
+//     72-byte links from four on (16 32 32 32 44.4 -> 40.1, 32^4 88.0 -> 78.0), of
+//     48-byte ones not (32^4 54.2 -> 59.1)
 //   SU(3) FP64, up to one: 16^4 12.2/20.5 -> 10.5/19.0; overrelaxation at any
-//     size (24^4 51.3 -> 46.1, 32^4 151 -> 137, two-row 32^4 101 -> 92), the
+//     size (24^4 51.3 -> 46.1, 32^4 151 -> 137, two-row 32^4 101 -> 92) unless it
+//     walks linearly over planes of more than twelve wavefronts (40^4 445 -> 458,
+//     44^4 696 -> 702; 36^4, of ten, 263 -> 261; 48^4, t-blocked, 936 -> 789); the
 //     heatbath not (20^4 36.3 -> 38.3)
 //   SU(3) with a direction absent: never.  The loads ahead are issued for it
 //     too, and a wavefront of fewer staples does better with others beside it
@@ -136,12 +151,15 @@ inline bool valid_phase_block(int b) { return b == 64 || b == 128 || b == 256; }
 // 48-byte links (FP32 two-row) and 8 for larger ones (18-real FP32 70.0 -> 67.3
 // us, FP64 161 -> 152); a grid of two wavefronts per SIMD needs none, nor a
 // t-blocked walk (16^4 8.5 -> 8.8 with one).
-inline Shape default_shape(int nc, bool f64, size_t link_bytes, long long links, bool full, bool heatbath) {
+inline Shape default_shape(int nc, bool f64, size_t link_bytes, const PhaseGrid& grid, bool heatbath) {
     const long long per_simd = 1024 * 64;  // links of one wavefront on every SIMD
     const long long few = nc != 3 ? 2 * per_simd : f64 ? per_simd : per_simd * 3 / 2;
-    if (links <= few && (nc != 3 || full)) return Shape{64, 1, 0, 0};
-    if (nc == 3 && full) {
-        const bool many = heatbath ? !f64 && link_bytes > 48 && links >= 4 * per_simd : f64 || links >= 6 * per_simd;
+    if (nc == 3 && !grid.full) return Shape{256, 1, heatbath ? 16 : link_bytes > 48 ? 8 : 12, 4};
+    if (grid.links <= few) return Shape{64, 1, 0, 0};
+    if (nc == 3) {
+        const bool many = heatbath ? !f64 && link_bytes > 48 && grid.links >= 4 * per_simd
+                          : f64    ? !grid.far
+                                   : grid.links >= (link_bytes > 48 ? 8 : 6) * per_simd;
         if (many) return Shape{64, 1, 8, 4};
     }
     return Shape{256, 1, heatbath ? 16 : link_bytes > 48 ? 8 : 12, 4};

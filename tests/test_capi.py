@@ -158,6 +158,14 @@ def test_create_validates_buffers_without_touching_them(lib):
     (3, (48, 48, 48, 1), 1, (256, 1, 16, 0), (256, 1, 8, 0)),
     (3, (128, 2, 16, 64), 3, (256, 1, 16, 0), (64, 1, 8, 4)),
     (3, (128, 1, 16, 64), 3, (256, 1, 16, 0), (256, 1, 8, 0)),
+    # the lines of the large SU(3) overrelaxation: links in hand, and planes
+    # walked linearly
+    (3, (24, 24, 40, 38), 0, (64, 1, 8, 0), (256, 1, 8, 0)),
+    (3, (32, 32, 32, 32), 0, (64, 1, 8, 4), (64, 1, 8, 4)),
+    (3, (24, 24, 40, 40), 2, (256, 1, 16, 0), (64, 1, 8, 0)),
+    (3, (40, 40, 40, 40), 1, (256, 1, 16, 0), (256, 1, 8, 0)),
+    (3, (36, 36, 36, 36), 3, (256, 1, 16, 0), (64, 1, 8, 0)),
+    (3, (48, 48, 32, 32), 1, (256, 1, 16, 0), (64, 1, 8, 4)),
     # SU(2) and SU(4), whose loads are not issued ahead, at either
     (4, (256, 256, 1, 1), 0, (64, 1, 0, 0), (64, 1, 0, 0)),
     # between the lines of the two kinds: the overrelaxation has a shape that
