@@ -373,7 +373,8 @@ int sun_set_launch(sun_lattice_t h, int kind, int block, int xcd, int waves, int
     if (int rc = check_shape(kind, block, waves, tblock)) return rc;
     for (int k = 0; k < 2; ++k)
         if (kind < 0 || kind == k)
-            h->shape[k] = sun::Shape{block, xcd ? 1 : 0, waves, tblock > 1 ? tblock : 0, h->shape[k].spt};
+            h->shape[k] = sun::Shape{block, xcd ? 1 : 0, waves, tblock > 1 ? tblock : 0, h->shape[k].spt,
+                                     h->shape[k].ahead};
     return SUN_OK;
 }
 
@@ -675,10 +676,13 @@ int sun_batch_create(int n, const sun_lattice_t* chains, const double* betas, co
                 if (p.far) far += p.links;
             }
             const sun_lattice_t h = chains[b->host[gr.first].out_index];
-            for (int k = 0; k < 2; ++k)
-                gr.shape[k].block = sun::default_shape(nc, is_f64(dt), h->link_bytes / (4 * (size_t)h->g.V),
-                                                       sun::PhaseGrid{links, 2 * full > links, 2 * far > links},
-                                                       k == SUN_HEATBATH).block;
+            for (int k = 0; k < 2; ++k) {
+                const sun::Shape sh = sun::default_shape(nc, is_f64(dt), h->link_bytes / (4 * (size_t)h->g.V),
+                                                         sun::PhaseGrid{links, 2 * full > links, 2 * far > links},
+                                                         k == SUN_HEATBATH);
+                gr.shape[k].block = sh.block;
+                gr.shape[k].ahead = sh.ahead;
+            }
         }
         b->groups.push_back(gr);
     }
@@ -752,7 +756,7 @@ int sun_batch_replay(sun_batch_t b, sun_stream_t stream) {
 int sun_batch_set_launch(sun_batch_t b, int kind, int block, int xcd, int waves) {
     if (!b) return fail(SUN_EINVAL, "null batch");
     if (int rc = check_shape(kind, block, waves)) return rc;
-    return batch_reshape(b, kind, [&](sun::Shape& sh) { sh = sun::Shape{block, xcd ? 1 : 0, waves, 0, sh.spt}; });
+    return batch_reshape(b, kind, [&](sun::Shape& sh) { sh = sun::Shape{block, xcd ? 1 : 0, waves, 0, sh.spt, sh.ahead}; });
 }
 
 int sun_batch_set_sites_per_item(sun_batch_t b, int kind, int spt) {

@@ -456,18 +456,17 @@ __device__ __forceinline__ void update_any(T2<T>* __restrict__ U, const Geom& g,
         update_link<N, T, R, HB, MU, NT, AHEAD>(U, g, par, h, beta, k0, k1, step);
 }
 
-// SU(3) phases in 64-item workgroups issue the staple's loads ahead; where
-// that pays is default_shape's choice of workgroup.  Wavefronts per SIMD that
-// their registers are meant for: two in FP32 (169 to 219 registers), one in
-// FP64 (262 and more; held to two it spills: 24^4 heatbath 68 -> 82 us).
-constexpr bool loads_ahead(int n, int block) { return n == 3 && block == 64; }
-template <int N, typename T>
-constexpr int max_waves(int block) {
-    return !loads_ahead(N, block) ? 8 : sizeof(T) == 4 ? 2 : 1;
+// AHEAD (SU(3), 64-item workgroups): the staple's loads are issued ahead;
+// default_shape says where.  Wavefronts per SIMD that those kernels' registers
+// are meant for: two in FP32 (169 to 219 registers), one in FP64 (262 and more;
+// held to two it spills: 24^4 heatbath 68 -> 82 us).
+template <typename T>
+constexpr int max_waves(bool ahead) {
+    return !ahead ? 8 : sizeof(T) == 4 ? 2 : 1;
 }
-template <int N, typename T>
-constexpr int min_waves(int block) {
-    return loads_ahead(N, block) ? max_waves<N, T>(block) : 1;
+template <typename T>
+constexpr int min_waves(bool ahead) {
+    return ahead ? max_waves<T>(true) : 1;
 }
 
 // One checkerboard phase of one lattice, BS work-items per workgroup; xcd
@@ -484,15 +483,15 @@ constexpr int min_waves(int block) {
 // Grid: ceil(nblk / walk.spt) workgroups over nblk tiles of BS sites; a
 // workgroup takes walk positions blockIdx.x + r gridDim.x, r < walk.spt, in
 // turn (r apart by a multiple of 8 when the grid is, so they stay on one XCD).
-template <int N, typename T, int R, bool HB, int MU, int BS, bool NT>
-__global__ __launch_bounds__(BS)
-    __attribute__((amdgpu_waves_per_eu(min_waves<N, T>(BS), max_waves<N, T>(BS)))) void k_update(T2<T>* __restrict__ U, Geom g, int par, T beta, uint32_t k0,
-                                               uint32_t k1, uint32_t step, Walk walk, int nblk) {
+template <int N, typename T, int R, bool HB, int MU, int BS, bool NT, bool AHEAD>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(min_waves<T>(AHEAD), max_waves<T>(AHEAD)))) void
+k_update(T2<T>* __restrict__ U, Geom g, int par, T beta, uint32_t k0, uint32_t k1, uint32_t step, Walk walk,
+         int nblk) {
     for (int r = 0; r < walk.spt; ++r) {
         const int b = (int)blockIdx.x + r * (int)gridDim.x;
         if (b >= nblk) break;
         const int h = walk_tile(b, nblk, walk) * BS + threadIdx.x;
-        if (h < g.Vh) update_any<N, T, R, HB, MU, NT, loads_ahead(N, BS)>(U, g, par, h, beta, k0, k1, step);
+        if (h < g.Vh) update_any<N, T, R, HB, MU, NT, AHEAD>(U, g, par, h, beta, k0, k1, step);
     }
 }
 
@@ -522,10 +521,9 @@ __device__ __forceinline__ int find_chain(const ChainDesc* __restrict__ d, int n
 // Batched phase: tile0[TILE_HALF_HB / _OR] counts tiles of BS work-items.
 // Grid: ceil(tiles / spt) workgroups; workgroup b takes tiles b + r gridDim.x,
 // r < spt, in turn.
-template <int N, typename T, int R, bool HB, int MU, int BS>
-__global__ __launch_bounds__(BS)
-    __attribute__((amdgpu_waves_per_eu(min_waves<N, T>(BS), max_waves<N, T>(BS)))) void k_update_batch(const ChainDesc* __restrict__ d, int n, int par,
-                                                     uint32_t step_offset, int xcd, int tiles, int spt) {
+template <int N, typename T, int R, bool HB, int MU, int BS, bool AHEAD>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(min_waves<T>(AHEAD), max_waves<T>(AHEAD)))) void
+k_update_batch(const ChainDesc* __restrict__ d, int n, int par, uint32_t step_offset, int xcd, int tiles, int spt) {
     constexpr int KIND = HB ? TILE_HALF_HB : TILE_HALF_OR;
     for (int r = 0; r < spt; ++r) {
         const int b = (int)blockIdx.x + r * (int)gridDim.x;
@@ -535,8 +533,8 @@ __global__ __launch_bounds__(BS)
         const Geom g = d[c].g;
         const int h = (tile - d[c].tile0[KIND]) * BS + threadIdx.x;
         if (h < g.Vh && ((g.present >> MU) & 1))
-            update_any<N, T, R, HB, MU, false, loads_ahead(N, BS)>((T2<T>*)d[c].links, g, par, h, (T)d[c].beta, d[c].k0,
-                                                                   d[c].k1, (uint32_t)(d[c].step + step_offset));
+            update_any<N, T, R, HB, MU, false, AHEAD>((T2<T>*)d[c].links, g, par, h, (T)d[c].beta, d[c].k0, d[c].k1,
+                                                      (uint32_t)(d[c].step + step_offset));
     }
 }
 

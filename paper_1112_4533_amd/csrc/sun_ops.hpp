@@ -16,6 +16,9 @@ struct Shape {
     int waves = 0;    // resident waves per CU (0 = no cap)
     int tblock = 0;   // time slices per block of the tile walk (0: linear)
     int spt = 1;      // sites per work-item (1, 2 or 4): tiles a workgroup takes in turn
+    // 64-item workgroups issue the staple's loads ahead (SU(3); fixed by the
+    // lattice, whatever shape is set)
+    bool ahead = false;
 };
 inline bool valid_spt(int s) { return s == 1 || s == 2 || s == 4; }
 inline int grid_for(int nblk, int spt) { return (nblk + spt - 1) / spt; }
@@ -119,10 +122,17 @@ inline PhaseGrid phase_grid(const Geom& g, bool linear) {  // linear: the walk i
 }
 
 // Workgroup, wave cap and walk that a phase starts with; a tuner or the caller
-// may replace them.  block 256 unless 64-item workgroups do better, which
-// spread a small grid over all CUs and, for SU(3), issue the staple's loads
-// ahead at half the resident wavefronts.  Overrelaxation / heatbath phase,
-// 256 -> 64, in microseconds:
+// may replace them, but not whether 64-item workgroups of SU(3) issue the loads
+// ahead: they do where they are the default, but for two stretches of the
+// overrelaxation in which they are faster with the loads by direction (FP32
+// 72-byte links from five quarters of a wavefront per SIMD to one and a half,
+// 20 20 20 24 16.1 -> 15.5; FP64 from one to one and a half, 20^4 24.7 -> 23.4,
+// 18 20 22 24 28.2 -> 27.4).  Where they are not the default, a 64-item shape that
+// is asked for has the loads by direction too (24^4 FP32 overrelaxation 28.0 ->
+// 26.9, FP64 heatbath 64.4 -> 60.6).  block 256 unless 64-item workgroups do
+// better, which spread a small grid over all CUs and, for SU(3), issue the
+// staple's loads ahead at half the resident wavefronts.  Overrelaxation /
+// heatbath phase, 256 -> 64, in microseconds:
 //   SU(2), SU(4), up to two wavefronts per SIMD: SU(2) FP32 20^4 6.0/7.3 ->
 //     5.3/7.0, SU(4) 16^4 FP32 18.6/23.0 -> 16.4/21.6, FP64 24.7/61.8 -> 23.4/53.9;
 //     past it equal (SU(4) 24^4 54.3/60.7, 55.0/59.9) or slower (SU(2) 32^4
@@ -137,8 +147,9 @@ inline PhaseGrid phase_grid(const Geom& g, bool linear) {  // linear: the walk i
 //     32^4 48.2 -> 46.8, 36^4 89.6 -> 84.8, 48^4 310 -> 289); heatbath of
 //     72-byte links from four on (16 32 32 32 44.4 -> 40.1, 32^4 88.0 -> 78.0), of
 //     48-byte ones not (32^4 54.2 -> 59.1)
-//   SU(3) FP64, up to one: 16^4 12.2/20.5 -> 10.5/19.0; overrelaxation at any
-//     size (24^4 51.3 -> 46.1, 32^4 151 -> 137, two-row 32^4 101 -> 92) unless it
+//   SU(3) FP64, up to one (144-byte links below it: 16 16 16 32 18.7/26.7 ->
+//     19.2/27.1, two-row 14.9/22.5 -> 14.2/22.4): 16^4 12.2/20.5 -> 10.5/19.0;
+//     overrelaxation at any size (24^4 51.3 -> 46.1, 32^4 151 -> 137, two-row 32^4 101 -> 92) unless it
 //     walks linearly over planes of more than twelve wavefronts (40^4 445 -> 458,
 //     44^4 696 -> 702; 36^4, of ten, 263 -> 261; 48^4, t-blocked, 936 -> 789); the
 //     heatbath not (20^4 36.3 -> 38.3)
@@ -153,14 +164,17 @@ inline PhaseGrid phase_grid(const Geom& g, bool linear) {  // linear: the walk i
 // t-blocked walk (16^4 8.5 -> 8.8 with one).
 inline Shape default_shape(int nc, bool f64, size_t link_bytes, const PhaseGrid& grid, bool heatbath) {
     const long long per_simd = 1024 * 64;  // links of one wavefront on every SIMD
-    const long long few = nc != 3 ? 2 * per_simd : f64 ? per_simd : per_simd * 3 / 2;
+    const long long few = nc != 3 ? 2 * per_simd : !f64 ? per_simd * 3 / 2 : link_bytes > 96 ? per_simd - 1 : per_simd;
     if (nc == 3 && !grid.full) return Shape{256, 1, heatbath ? 16 : link_bytes > 48 ? 8 : 12, 4};
-    if (grid.links <= few) return Shape{64, 1, 0, 0};
+    if (grid.links <= few) {
+        const bool late = !f64 && !heatbath && link_bytes > 48 && grid.links > per_simd * 5 / 4;
+        return Shape{64, 1, 0, 0, 1, nc == 3 && !late};
+    }
     if (nc == 3) {
-        const bool many = heatbath ? !f64 && link_bytes > 48 && grid.links >= 4 * per_simd
-                          : f64    ? !grid.far
+        if (f64 && !heatbath && !grid.far) return Shape{64, 1, 8, 4, 1, grid.links > per_simd * 3 / 2};
+        const bool many = heatbath ? link_bytes > 48 && grid.links >= 4 * per_simd
                                    : grid.links >= (link_bytes > 48 ? 8 : 6) * per_simd;
-        if (many) return Shape{64, 1, 8, 4};
+        if (!f64 && many) return Shape{64, 1, 8, 4, 1, true};
     }
     return Shape{256, 1, heatbath ? 16 : link_bytes > 48 ? 8 : 12, 4};
 }

@@ -10,7 +10,7 @@ template <int N, typename T, int R>
 struct OpsImpl {
     using P = T2<T>;
 
-    template <bool HB, int MU, int BS>
+    template <bool HB, int MU, int BS, bool AHEAD = false>
     static void update_bs(const Ctx& c, int par, T beta, uint32_t k0, uint32_t k1, uint32_t step, int lds,
                           const Walk& w) {
         P* u = (P*)c.links;
@@ -18,9 +18,11 @@ struct OpsImpl {
         Walk wk = w;
         if (c.order) random_tile_order(c.order, nblk, wk);
         if (c.nt)
-            k_update<N, T, R, HB, MU, BS, true><<<grid, BS, lds, c.stream>>>(u, c.g, par, beta, k0, k1, step, wk, nblk);
+            k_update<N, T, R, HB, MU, BS, true, AHEAD><<<grid, BS, lds, c.stream>>>(u, c.g, par, beta, k0, k1, step, wk,
+                                                                                  nblk);
         else
-            k_update<N, T, R, HB, MU, BS, false><<<grid, BS, lds, c.stream>>>(u, c.g, par, beta, k0, k1, step, wk, nblk);
+            k_update<N, T, R, HB, MU, BS, false, AHEAD><<<grid, BS, lds, c.stream>>>(u, c.g, par, beta, k0, k1, step,
+                                                                                   wk, nblk);
     }
 
     template <bool HB, int MU>
@@ -29,6 +31,12 @@ struct OpsImpl {
         const int lds = lds_for_wave_cap(sh.waves, sh.block);
         Walk w = walk_for(c.g, sh);
         w.rev = c.rev;
+        if constexpr (N == 3) {
+            if (sh.block == 64 && sh.ahead) {
+                update_bs<HB, MU, 64, true>(c, par, beta, k0, k1, step, lds, w);
+                return;
+            }
+        }
         switch (sh.block) {
             case 64: update_bs<HB, MU, 64>(c, par, beta, k0, k1, step, lds, w); break;
             case 128: update_bs<HB, MU, 128>(c, par, beta, k0, k1, step, lds, w); break;
@@ -36,21 +44,33 @@ struct OpsImpl {
         }
     }
 
-    template <bool HB, int BS>
+    template <bool HB, int MU, int BS, bool AHEAD>
+    static void launch_batch(const ChainDesc* d, int n, int grid, int par, uint32_t off, int xcd, int tiles, int spt,
+                             int lds, hipStream_t s) {
+        k_update_batch<N, T, R, HB, MU, BS, AHEAD><<<grid, BS, lds, s>>>(d, n, par, off, xcd, tiles, spt);
+    }
+
+    template <bool HB, int BS, bool AHEAD = false>
     static void update_batch_bs(const ChainDesc* d, int n, int tiles, int mu, int par, uint32_t off, int xcd,
                                 int spt, int lds, hipStream_t s) {
         const int grid = grid_for(tiles, spt);
         switch (mu) {
-            case 0: k_update_batch<N, T, R, HB, 0, BS><<<grid, BS, lds, s>>>(d, n, par, off, xcd, tiles, spt); break;
-            case 1: k_update_batch<N, T, R, HB, 1, BS><<<grid, BS, lds, s>>>(d, n, par, off, xcd, tiles, spt); break;
-            case 2: k_update_batch<N, T, R, HB, 2, BS><<<grid, BS, lds, s>>>(d, n, par, off, xcd, tiles, spt); break;
-            default: k_update_batch<N, T, R, HB, 3, BS><<<grid, BS, lds, s>>>(d, n, par, off, xcd, tiles, spt); break;
+            case 0: launch_batch<HB, 0, BS, AHEAD>(d, n, grid, par, off, xcd, tiles, spt, lds, s); break;
+            case 1: launch_batch<HB, 1, BS, AHEAD>(d, n, grid, par, off, xcd, tiles, spt, lds, s); break;
+            case 2: launch_batch<HB, 2, BS, AHEAD>(d, n, grid, par, off, xcd, tiles, spt, lds, s); break;
+            default: launch_batch<HB, 3, BS, AHEAD>(d, n, grid, par, off, xcd, tiles, spt, lds, s); break;
         }
     }
 
     template <bool HB>
     static void update_batch_kind(const ChainDesc* d, int n, int tiles, int mu, int par, uint32_t off,
                                   const Shape& sh, int lds, hipStream_t s) {
+        if constexpr (N == 3) {
+            if (sh.block == 64 && sh.ahead) {
+                update_batch_bs<HB, 64, true>(d, n, tiles, mu, par, off, sh.xcd, sh.spt, lds, s);
+                return;
+            }
+        }
         switch (sh.block) {
             case 64: update_batch_bs<HB, 64>(d, n, tiles, mu, par, off, sh.xcd, sh.spt, lds, s); break;
             case 128: update_batch_bs<HB, 128>(d, n, tiles, mu, par, off, sh.xcd, sh.spt, lds, s); break;

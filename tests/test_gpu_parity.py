@@ -780,6 +780,31 @@ def test_launch_shapes_past_the_small_lattices(gpu, nc, dtype, L):
         assert torch.equal(ref.links, lat.links), (shape, spt)
 
 
+@pytest.mark.parametrize("dtype,L", [("f32", (32, 16, 10, 8)), ("f32", (32, 32, 32, 8)), ("f32r12", (32, 32, 32, 8)),
+                                      ("f64", (32, 32, 16, 10)), ("f64r12", (32, 32, 16, 14)),
+                                      ("f32", (20, 20, 20, 24)),
+                                      ("f32", (64, 32, 1, 32))])
+def test_su3_workgroups_of_64_on_either_side_of_their_lines(gpu, dtype, L):
+    """SU(3) shapes of 64 items issue the staple's loads ahead only where they
+    are the default (here: the first lattice, and the overrelaxation of
+    the larger FP64 one); asked for elsewhere they do not.  The same bits as 256 items either way, alone
+    and in a batch."""
+    sun = gpu
+    fields = []
+    for shape, batched in [((256, 1, 0, 0), False), ((64, 1, 0, 0), False), ((64, 1, 8, 8), False), ((64, 0, 0, 0), True)]:
+        lat = gpu_lattice(sun, 3, L, dtype, hot=True, seed=8)
+        if batched:
+            bt = sun.Batch([lat], [BETA[3]], [8])
+            bt.set_launch(*shape[:3])
+            bt.sweep(1, 2)
+        else:
+            lat.set_launch(*shape)
+            lat.sweep(BETA[3], 1, 2, seed=8)
+        torch.cuda.synchronize()
+        fields.append(lat.links)
+    assert all(torch.equal(fields[0], f) for f in fields[1:])
+
+
 @pytest.mark.parametrize("nc,dtype,L", [(3, "f32r12", (16, 16, 4, 8)), (3, "f64", (6, 4, 2, 6)),
                                          (2, "f32", (8, 8, 8, 8)), (4, "f32", (4, 4, 4, 4))])
 def test_random_tile_orders_give_the_same_bits(gpu, nc, dtype, L):
