@@ -832,6 +832,57 @@ def test_random_tile_orders_give_the_same_bits(gpu, nc, dtype, L):
     lat.set_tile_order(0)
 
 
+# Lattices past the four-lanes-per-link form, whose (x, y) planes hold whole
+# workgroups of every size and whose L_t every walk divides.
+ONE_LANE = [(2, "f32", (32, 16, 18, 8)), (3, "f32", (32, 16, 10, 8)), (3, "f32r12", (32, 32, 32, 8)),
+            (3, "f64", (32, 16, 10, 8)), (4, "f32", (32, 16, 12, 8))]
+
+
+@pytest.mark.parametrize("nc,dtype,L", ONE_LANE)
+def test_every_launch_shape_of_the_one_lane_phases(gpu, nc, dtype, L):
+    """As test_every_launch_shape_gives_the_same_bits, on lattices whose
+    phases take the shape: every workgroup size, order, wave cap and walk, and
+    1, 2 or 4 sites per work-item, the same bits as a batch's linear walk."""
+    sun = gpu
+    ref = gpu_lattice(sun, nc, L, dtype, hot=True, seed=8)
+    bt = sun.Batch([ref], [BETA[nc]], [8])
+    bt.set_launch(256, 0, 0)
+    bt.sweep(1, 1)
+    lat = gpu_lattice(sun, nc, L, dtype, hot=True, seed=8)
+    start = lat.links.clone()
+    for spt in sun.Lattice.SITES_PER_ITEM:
+        for shape in sun.Lattice.LAUNCH_SHAPES:
+            if spt > 1 and shape[2] not in (0, 12):
+                continue
+            lat.links.copy_(start)
+            lat.step = 0
+            lat.set_sites_per_item(spt)
+            lat.set_launch(*shape)
+            assert lat.launch == (shape, shape)
+            lat.sweep(BETA[nc], 1, 1, seed=8)
+            assert torch.equal(ref.links, lat.links), (shape, spt)
+
+
+@pytest.mark.parametrize("nc,dtype,L", ONE_LANE)
+def test_random_tile_orders_of_the_one_lane_phases(gpu, nc, dtype, L):
+    """The race canary of test_random_tile_orders_give_the_same_bits on
+    lattices whose phases walk tiles by their launch shape."""
+    sun = gpu
+    lat = gpu_lattice(sun, nc, L, dtype, hot=True, seed=8)
+    start = lat.links.clone()
+    lat.sweep(BETA[nc], 1, 2, seed=8)
+    want = lat.links.clone()
+    for seed, shape, spt in [(1, (256, 1, 12, 4), 1), (2, (64, 0, 0, 0), 1), (3, (128, 1, 16, 8), 2),
+                             (4, (64, 1, 8, 2), 4), (0xDEADBEEF, (256, 1, 0, 0), 4)]:
+        lat.links.copy_(start)
+        lat.step = 0
+        lat.set_launch(*shape)
+        lat.set_sites_per_item(spt)
+        lat.set_tile_order(seed)
+        lat.sweep(BETA[nc], 1, 2, seed=8)
+        assert torch.equal(want, lat.links), (seed, shape, spt)
+
+
 def test_batch_launch_shapes_and_tuner(gpu, tmp_path, monkeypatch):
     sun = gpu
     from paper_1112_4533_amd import autotune
