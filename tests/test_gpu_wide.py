@@ -450,6 +450,12 @@ def test_wide_reunitarize_row_layouts(gpu, nc, noise):
     assert to_np(lat.unitarity()).max() < 1e-13
 
 
+@pytest.mark.parametrize("nc,noise", [(18, 1e-3), (19, 1e-3), (17, 1.0), (18, 1.0)])
+def test_wide_reunitarize_nine_columns(gpu, nc, noise):
+    """The layout with nine columns to a lane, to its last Nc and past it."""
+    test_wide_reunitarize_row_layouts(gpu, nc, noise)
+
+
 @pytest.mark.parametrize("nc,dtype", [(4, "f64w"), (5, "f32"), (6, "f64"), (8, "f32"), (12, "f64"), (13, "f32"),
                                       (16, "f64"), (25, "f32"), (32, "f64")])
 def test_wide_singular_links_have_determinant_zero(gpu, nc, dtype):
