@@ -17,6 +17,17 @@ void with_small(int nc, F f) {
     }
 }
 
+// f(form) for Nc > kWideSmallMax
+template <typename F>
+void with_form(int nc, F f) {
+    if (nc <= wide::kTile)
+        f(std::integral_constant<int, wide::PLAQ_ONE>{});
+    else if (nc <= wide::kEdgeMax)
+        f(std::integral_constant<int, wide::PLAQ_EDGES>{});
+    else
+        f(std::integral_constant<int, wide::PLAQ_FOUR>{});
+}
+
 }  // namespace
 
 template <typename T>
@@ -29,12 +40,12 @@ void launch_plaquette_wide(const Ctx& c, double* partial) {
             wide::k_plaquette_small<T, N><<<tiles, wide::kLanes, wide::plaq_small_lds<T, N>(), c.stream>>>(u, c.g,
                                                                                                            partial);
         });
-    else if (c.nc <= wide::kTile)
-        wide::k_plaquette_large<T, false><<<tiles, wide::plaq_threads<false>(), wide::plaq_large_lds<T>(c.nc),
-                                            c.stream>>>(u, c.g, c.nc, partial);
     else
-        wide::k_plaquette_large<T, true><<<tiles, wide::plaq_threads<true>(), wide::plaq_large_lds<T>(c.nc),
-                                           c.stream>>>(u, c.g, c.nc, partial);
+        with_form(c.nc, [&](auto form) {
+            constexpr int F = decltype(form)::value;
+            wide::k_plaquette_large<T, F><<<tiles, wide::plaq_threads(F), wide::plaq_large_lds<T>(c.nc), c.stream>>>(
+                u, c.g, c.nc, partial);
+        });
 }
 template <typename T>
 void launch_plaquette_wide_batch(const ChainDesc* d, int n, int tiles, int nc, hipStream_t s) {
@@ -43,12 +54,12 @@ void launch_plaquette_wide_batch(const ChainDesc* d, int n, int tiles, int nc, h
             constexpr int N = decltype(k)::value;
             wide::k_plaquette_small_batch<T, N><<<tiles, wide::kLanes, wide::plaq_small_lds<T, N>(), s>>>(d, n);
         });
-    else if (nc <= wide::kTile)
-        wide::k_plaquette_large_batch<T, false><<<tiles, wide::plaq_threads<false>(), wide::plaq_large_lds<T>(nc), s>>>(
-            d, n, nc);
     else
-        wide::k_plaquette_large_batch<T, true><<<tiles, wide::plaq_threads<true>(), wide::plaq_large_lds<T>(nc), s>>>(
-            d, n, nc);
+        with_form(nc, [&](auto form) {
+            constexpr int F = decltype(form)::value;
+            wide::k_plaquette_large_batch<T, F><<<tiles, wide::plaq_threads(F), wide::plaq_large_lds<T>(nc), s>>>(d, n,
+                                                                                                                  nc);
+        });
 }
 
 template void launch_plaquette_wide<float>(const Ctx&, double*);

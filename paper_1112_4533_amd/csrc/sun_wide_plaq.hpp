@@ -5,14 +5,15 @@
 //
 // Up to Nc = 8 a wavefront takes four sites, sixteen lanes each (row r and
 // column half of H and K per lane, as in the update); above, the products
-// are 16 x 16 FP64 matrix-core tiles, one wavefront per tile (one to Nc = 16,
-// four above).  The links of the next product load while this one runs.
+// are 16 x 16 FP64 matrix-core tiles: one on one wavefront to Nc = 20, with what
+// lies past it from Nc = 17 on the vector units, then four on four wavefronts.
+// The links of the next product load while this one runs.
 //
-// Bound by the FP64 rate (Nc >= 17: the tiles' padding included) and the
+// Bound by the FP64 rate (Nc >= 21: the tiles' padding included) and the
 // links' re-reads through L2.  Against one wavefront per site, products and
 // one factor through LDS: SU(6) FP32 12^4 106 -> 37 us, SU(8) FP64 12^4 130 -> 64,
-// SU(16) FP64 8^4 116 -> 48, SU(24) FP64 8^4 510 -> 214, SU(32) FP32 8^4 1357 ->
-// 269; at Nc = 17, where the padding is worst, 165 -> 178.
+// SU(16) FP64 8^4 116 -> 48, SU(17) FP32 8^4 151 -> 82, SU(24) FP64 8^4 510 -> 214,
+// SU(32) FP32 8^4 1357 -> 269.
 #pragma once
 
 #include "sun_wide_large.hpp"
@@ -173,21 +174,64 @@ struct PlaqTile {
     }
 };
 
-template <bool BIG>
-constexpr int plaq_threads() {
-    return BIG ? 4 * kLanes : kLanes;
+// Forms: one wavefront and one tile to Nc = 16; the same up to kEdgeMax with the
+// rows and columns past 15 on the vector units; four wavefronts and tiles above.
+enum PlaqForm { PLAQ_ONE, PLAQ_EDGES, PLAQ_FOUR };
+constexpr int kEdgeMax = kTile + 4;
+constexpr int plaq_threads(int form) { return form == PLAQ_FOUR ? 4 * kLanes : kLanes; }
+constexpr int plaq_loads(int form) {  // entries of a link per work-item
+    const int n = form == PLAQ_ONE ? kTile : form == PLAQ_EDGES ? kEdgeMax : kNcMax;
+    return (n * n + plaq_threads(form) - 1) / plaq_threads(form);
 }
 template <typename T>
 constexpr size_t plaq_large_lds(int n) {
     return (size_t)2 * mat_entries(n) * sizeof(T2<T>);
 }
 
+// The entries of A B in rows or columns past 15, kTile < n <= kEdgeMax: lane l
+// sums entries l, l + 64, ... of the rows past 15 and then of the columns past
+// 15 in the rows above them.  Four tiles would spend three quarters of the
+// matrix cores' time on them: SU(17) on 8^4 FP32 169 us against 82, FP64 177
+// against 88 (one wavefront per site with products through LDS: 151 and 157),
+// SU(20) 181 against 137 and 188 against 141.
+struct PlaqEdges {
+    static constexpr int kMost = (kEdgeMax * kEdgeMax - kTile * kTile + kLanes - 1) / kLanes;
+    double re[kMost], im[kMost];
+    static __device__ __forceinline__ int count(int n) { return n * n - kTile * kTile; }
+    template <typename T>
+    __device__ __forceinline__ void product(const T2<T>* A, const T2<T>* B, int n, int ns) {
+        const int l = fresh_lane(), past = n - kTile, in_rows = past * n;
+#pragma unroll
+        for (int q = 0; q < kMost; ++q) {
+            re[q] = im[q] = 0.0;
+            if (q * kLanes >= count(n)) continue;  // the same on all lanes
+            const int e = min(l + q * kLanes, count(n) - 1), c = e - in_rows;
+            const int i = c < 0 ? kTile + e / n : c / past, j = c < 0 ? e % n : kTile + c % past;
+            const T2<T>* a = A + i * ns;
+            const T2<T>* b = B + j;
+#pragma unroll 4
+            for (int k = 0; k < n; ++k) {
+                const T2<T> x = a[k], y = b[k * ns];
+                cmac(re[q], im[q], (double)x.x, (double)x.y, (double)y.x, (double)y.y);
+            }
+        }
+    }
+    // Re sum over the lane's entries of this conj(o)
+    __device__ __forceinline__ double dot(const PlaqEdges& o, int n) const {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < kMost; ++q)
+            if ((int)threadIdx.x + q * kLanes < count(n)) t = fmadd(im[q], o.im[q], fmadd(re[q], o.re[q], t));
+        return t;
+    }
+};
+
 // Sums of site s (as above), one wavefront per tile.
-template <typename T, bool BIG>
+template <typename T, int FORM>
 __device__ __forceinline__ void plaquette_site_large(const T2<T>* __restrict__ U, const Geom& g, int n, int s,
                                                      double* __restrict__ partial) {
-    constexpr int kThreads = plaq_threads<BIG>();
-    constexpr int kLoads = (BIG ? kNcMax * kNcMax : kTile * kTile) / kThreads;
+    constexpr bool BIG = FORM == PLAQ_FOUR;
+    constexpr int kThreads = plaq_threads(FORM), kLoads = plaq_loads(FORM);
     extern __shared__ double4 smem_plaq[];
     __shared__ double wave_acc[2 * kThreads / kLanes];
     const int n2 = n * n, ns = row_stride(n);
@@ -215,11 +259,13 @@ __device__ __forceinline__ void plaquette_site_large(const T2<T>* __restrict__ U
     if (!pl.done()) load(pl.mu, pl.nu);
     while (!pl.done()) {
         PlaqTile H, K;
+        PlaqEdges he, ke;
         fa.store(A, place);
         fb.store(B, place);
         load(pl.nu, pl.mu);
         __syncthreads();
         H.product<T>(A, B, n, ns, row0, col0);
+        if constexpr (FORM == PLAQ_EDGES) he.product<T>(A, B, n, ns);
         __syncthreads();
         fa.store(A, place);
         fb.store(B, place);
@@ -228,13 +274,16 @@ __device__ __forceinline__ void plaquette_site_large(const T2<T>* __restrict__ U
         if (!pl.done()) load(pl.mu, pl.nu);
         __syncthreads();
         K.product<T>(A, B, n, ns, row0, col0);
+        if constexpr (FORM == PLAQ_EDGES) ke.product<T>(A, B, n, ns);
         __syncthreads();
         double t = 0.0;
         const int l = fresh_lane();
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (row0 + tile_row<double>(l, r) < n) t = fmadd(H.im[r], K.im[r], fmadd(H.re[r], K.re[r], t));
-        if (col0 + (l & 15) < n) (with_time ? time : space) += t;
+        if (col0 + (l & 15) >= n) t = 0.0;
+        if constexpr (FORM == PLAQ_EDGES) t += he.dot(ke, n);
+        (with_time ? time : space) += t;
     }
     const double sums[2] = {wave_sum(space), wave_sum(time)};
     if constexpr (BIG) {
@@ -252,17 +301,17 @@ __device__ __forceinline__ void plaquette_site_large(const T2<T>* __restrict__ U
     }
 }
 
-template <typename T, bool BIG>
-__global__ __launch_bounds__(plaq_threads<BIG>()) void k_plaquette_large(const T2<T>* __restrict__ U, Geom g, int n,
+template <typename T, int FORM>
+__global__ __launch_bounds__(plaq_threads(FORM)) void k_plaquette_large(const T2<T>* __restrict__ U, Geom g, int n,
                                                                          double* __restrict__ partial) {
-    plaquette_site_large<T, BIG>(U, g, n, xcd_tile((int)blockIdx.x, (int)gridDim.x), partial);
+    plaquette_site_large<T, FORM>(U, g, n, xcd_tile((int)blockIdx.x, (int)gridDim.x), partial);
 }
-template <typename T, bool BIG>
-__global__ __launch_bounds__(plaq_threads<BIG>()) void k_plaquette_large_batch(const ChainDesc* __restrict__ d,
+template <typename T, int FORM>
+__global__ __launch_bounds__(plaq_threads(FORM)) void k_plaquette_large_batch(const ChainDesc* __restrict__ d,
                                                                                int nchains, int n) {
     const int tile = xcd_tile((int)blockIdx.x, (int)gridDim.x);
     const int c = find_chain<TILE_SITE>(d, nchains, tile);
-    plaquette_site_large<T, BIG>((const T2<T>*)d[c].links, d[c].g, n, tile - d[c].tile0[TILE_SITE], d[c].scratch);
+    plaquette_site_large<T, FORM>((const T2<T>*)d[c].links, d[c].g, n, tile - d[c].tile0[TILE_SITE], d[c].scratch);
 }
 
 }  // namespace wide

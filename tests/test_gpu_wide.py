@@ -450,6 +450,14 @@ def test_wide_reunitarize_row_layouts(gpu, nc, noise):
     assert to_np(lat.unitarity()).max() < 1e-13
 
 
+@pytest.mark.parametrize("nc,dtype,L", [(17, "f32", (2, 2, 2, 2)), (18, "f64", (4, 2, 2, 1)), (19, "f32", (2, 2, 2, 4)),
+                                        (20, "f64", (2, 2, 2, 2)), (21, "f32", (2, 2, 2, 2))])
+def test_wide_plaquette_rows_and_columns_past_a_tile(gpu, nc, dtype, L):
+    """Nc = 17 ... 20: one tile and its rows and columns past 15 (33, 68, 105
+    and 144 entries); the first Nc of the four tiles after them."""
+    test_wide_plaquette_of_every_tile_form(gpu, nc, dtype, L)
+
+
 @pytest.mark.parametrize("nc,noise", [(18, 1e-3), (19, 1e-3), (17, 1.0), (18, 1.0)])
 def test_wide_reunitarize_nine_columns(gpu, nc, noise):
     """The layout with nine columns to a lane, to its last Nc and past it."""
