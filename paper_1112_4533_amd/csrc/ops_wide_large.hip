@@ -32,10 +32,12 @@ void with_range(int nc, int hb, F f) {
     };
     if (nc <= wide::kLargeMax[0])
         kind(std::integral_constant<int, 0>{});
-    else if (nc <= (hb && sizeof(T) == 8 ? 22 : wide::kLargeMax[1]))
+    else if (nc <= wide::kLargeMax[1])
         kind(std::integral_constant<int, 1>{});
-    else
+    else if (nc <= (hb && sizeof(T) == 8 ? 22 : wide::kLargeMax[2]))
         kind(std::integral_constant<int, 2>{});
+    else
+        kind(std::integral_constant<int, 3>{});
 }
 
 }  // namespace

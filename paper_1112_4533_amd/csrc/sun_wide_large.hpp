@@ -23,9 +23,8 @@
 // unpadded LDS rows) and draws moved between lanes, 8^4, us per phase,
 // overrelaxation and heatbath: SU(12) FP32 44 -> 30 and 74 -> 38, SU(16) FP64
 // 89 -> 53 and 184 -> 93, SU(24) FP64 241 -> 191 and 436 -> 346, SU(32) FP32
-// 228 -> 155 and 404 -> 196, SU(32) FP64 553 -> 387 and 881 -> 556.  From 17 to
-// 19 in FP64 the padded tiles cost the overrelaxation 6% (SU(17) 122 -> 130)
-// and the heatbath gains 21% (226 -> 178).
+// 228 -> 155 and 404 -> 196, SU(32) FP64 553 -> 387 and 881 -> 556; where the
+// tiles are padded most, SU(17) FP64, 122 -> 115 and 226 -> 160.
 #pragma once
 
 #include <type_traits>
@@ -43,9 +42,11 @@ static_assert(kBatchSlots * kSlotSteps * kRecLanes == kLanes, "a batch's draws f
 constexpr int kTile = 16;       // largest Nc of the one-tile form
 constexpr int kMfmaMinN = 20;   // largest Nc whose FP32 products keep one k's terms together
 
-// Ranges of Nc compiled apart: up to 16 (one 16 x 16 tile), to 25 and to 32
-// (entries of a link per lane: 2, 5, 8).
-constexpr int kLargeMax[3] = {kTile, 25, kNcMax};
+// Ranges of Nc compiled apart: up to 16 (one 16 x 16 tile), to 19, to 25 and to
+// 32 (entries of a link per lane: 2, 3, 5, 8).  With five entries a lane the
+// FP64 overrelaxation of SU(17) spilled and took 125 us, SU(19) 142; with three
+// 115 and 131.
+constexpr int kLargeMax[4] = {kTile, 19, 25, kNcMax};
 constexpr int large_loads(int range) {
     return (kLargeMax[range] * kLargeMax[range] + kLargeThreads - 1) / kLargeThreads;
 }
@@ -522,7 +523,7 @@ __device__ __forceinline__ void update_link_large(T2<T>* __restrict__ U, const G
 
 // Wavefronts per SIMD the registers allow: four (eight links on a CU) except
 // for the FP64 tiles above Nc = 25, whose LDS leaves at most six links a CU.
-constexpr int large_waves(int range, bool f64) { return f64 && range == 2 ? 3 : 4; }
+constexpr int large_waves(int range, bool f64) { return f64 && range == 3 ? 3 : 4; }
 
 // One phase of one lattice, workgroups in the XCD-aware order.
 template <typename T, int RANGE, bool HB>

@@ -399,6 +399,13 @@ def test_wide_two_wavefronts_at_the_edges_of_their_ranges(gpu, nc, dtype):
         compare_links(got, want, dtype, m, k, f"nc={nc} {dtype} kind={kind} beta={beta}", spread=sp, decisions=dec)
 
 
+@pytest.mark.parametrize("nc,dtype", [(19, "f32"), (19, "f64"), (20, "f64")])
+def test_wide_three_entries_to_a_lane(gpu, nc, dtype):
+    """The last Nc of the form with three entries of a link to a lane, and the
+    first past it."""
+    test_wide_two_wavefronts_at_the_edges_of_their_ranges(gpu, nc, dtype)
+
+
 @pytest.mark.parametrize("nc,dtype", [(6, "f32"), (8, "f64"), (9, "f32"), (22, "f64"), (23, "f64")])
 @pytest.mark.parametrize("scale", [0.02, 0.3])
 def test_wide_heatbath_in_the_creutz_range(gpu, nc, dtype, scale):
