@@ -9,12 +9,12 @@ namespace {
 template <typename T, int RANGE, bool HB>
 void launch(const Ctx& c, int mu, int par, double beta, uint32_t k0, uint32_t k1, uint32_t step) {
     wide::k_update_large<T, RANGE, HB><<<wide_update_tiles(c.nc, c.g.Vh), wide::kLargeThreads,
-                                         wide::large_lds<T>(c.nc, HB), c.stream>>>((T2<T>*)c.links, c.g, c.nc, mu, par,
+                                         wide::large_lds<T, RANGE>(c.nc, HB), c.stream>>>((T2<T>*)c.links, c.g, c.nc, mu, par,
                                                                                    (T)beta, k0, k1, step);
 }
 template <typename T, int RANGE, bool HB>
 void launch_batch(const ChainDesc* d, int n, int tiles, int mu, int par, uint32_t off, int nc, hipStream_t s) {
-    wide::k_update_large_batch<T, RANGE, HB><<<tiles, wide::kLargeThreads, wide::large_lds<T>(nc, HB), s>>>(
+    wide::k_update_large_batch<T, RANGE, HB><<<tiles, wide::kLargeThreads, wide::large_lds<T, RANGE>(nc, HB), s>>>(
         d, n, nc, mu, par, off);
 }
 

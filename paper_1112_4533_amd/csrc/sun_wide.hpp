@@ -302,10 +302,11 @@ __device__ __forceinline__ T chain_unit_quat(const Quat<T>& p, Quat<T>& v) {
 constexpr int kPlaceLanes = 16;
 constexpr int kQuickHits = 3;              // attempts a record holds
 constexpr int kRecLanes = kQuickHits + 1;  // lanes that fill one: its attempts and its direction
-// C of the attempts can be taken in the Creutz range too: three up to Nc = 8,
-// two above (with three, FP64 records at Nc = 21 would leave 7 links to a CU).
-template <typename T, int C = 2>
-struct alignas(16) DrawRec {
+// C of the attempts can be taken in the Creutz range too: three up to Nc = 8
+// and in the largest form, two between (with three, FP64 records at Nc = 21
+// would leave 7 links to a CU).
+template <typename T, int C = 2, int ALIGN = 16>
+struct alignas(ALIGN) DrawRec {
     T kp[kQuickHits], r3sq[kQuickHits];
     T cos_t, sin_t, cos_p, sin_p;
     uint32_t w0[C], w1[C];  // the words a Creutz attempt takes
@@ -313,8 +314,8 @@ struct alignas(16) DrawRec {
 
 // Share q of a record: attempt q, or the direction (q = kQuickHits).  One
 // Philox call and one cosine serve both kinds.
-template <typename T, int C>
-__device__ __forceinline__ void fill_draw(DrawRec<T, C>& rec, int q, uint32_t k0, uint32_t k1, uint32_t site,
+template <typename T, int C, int A>
+__device__ __forceinline__ void fill_draw(DrawRec<T, C, A>& rec, int q, uint32_t k0, uint32_t k1, uint32_t site,
                                           uint32_t step, uint32_t mu_sg) {
     const bool dir = q == kQuickHits;
     const U4 w = philox(site, step, mu_sg, dir ? RNG_DIRECTION << 24 : (RNG_ATTEMPT << 24) | (uint32_t)q, k0, k1);
@@ -340,8 +341,8 @@ __device__ __forceinline__ void fill_draw(DrawRec<T, C>& rec, int q, uint32_t k0
 
 // The records of subgroups sg0 .. sg0 + nsteps - 1, by the sixteen lanes of
 // a place, four at a time.
-template <typename T, int C>
-__device__ __forceinline__ void fill_draws(DrawRec<T, C>* rec, int nsteps, uint32_t sg0, uint32_t k0, uint32_t k1,
+template <typename T, int C, int A>
+__device__ __forceinline__ void fill_draws(DrawRec<T, C, A>* rec, int nsteps, uint32_t sg0, uint32_t k0, uint32_t k1,
                                            uint32_t site, uint32_t step, uint32_t mu_hi) {
     const int q = (int)threadIdx.x % kPlaceLanes;
     for (int t0 = 0; t0 < nsteps; t0 += kPlaceLanes / kRecLanes) {
@@ -353,8 +354,8 @@ __device__ __forceinline__ void fill_draws(DrawRec<T, C>* rec, int nsteps, uint3
 // The draw of the lane's place: alpha and live (a step is there) are the
 // same on its sixteen lanes.  Returns the number of the accepted attempt
 // (1-based), or 0 (skip the step) when all kMaxAttempts were rejected.
-template <typename T, int C>
-__device__ __forceinline__ int place_draw(T alpha, bool live, const DrawRec<T, C>& rec, uint32_t k0, uint32_t k1,
+template <typename T, int C, int A>
+__device__ __forceinline__ int place_draw(T alpha, bool live, const DrawRec<T, C, A>& rec, uint32_t k0, uint32_t k1,
                                           uint32_t site, uint32_t step, uint32_t mu_sg, Quat<T>& x) {
     const bool creutz = alpha < Const<T>::switch_alpha;
     const T ia = chain_inverse(alpha);

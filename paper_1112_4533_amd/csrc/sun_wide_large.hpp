@@ -58,16 +58,29 @@ __host__ __device__ constexpr int row_count(int n) { return n + (n & 1); }
 __host__ __device__ constexpr int row_stride(int n) { return row_count(n) + 1; }
 __host__ __device__ constexpr int mat_entries(int n) { return row_count(n) * row_stride(n); }
 
+// Attempts of a record that a Creutz draw can take: three in the last range's
+// FP64 heatbath, which its registers hold to six links a CU whatever the LDS
+// (with two, SU(24) 8^4 at beta 6.2, nearly all draws Creutz, ran 494 us a
+// phase), elsewhere two.
+template <typename T>
+constexpr int creutz_words(int range) {
+    return sizeof(T) == 8 && range == 3 ? 3 : 2;
+}
+
 // LDS after the two matrices: the rotations of two batches, and (heatbath)
 // the draw records of two batches.
-template <typename T>
+template <typename T, int RANGE>
 struct alignas(16) LargeRing {
     Quat<T> a[2][kBatchSlots][kSlotSteps];
-    DrawRec<T> draw[2][kBatchSlots * kSlotSteps];
+    // records of three words without padding: SU(26) FP64 with it has 5 links on
+    // a CU instead of 6 (heatbath 358 -> 387 us)
+    static constexpr int kWords = creutz_words<T>(RANGE);
+    DrawRec<T, kWords, kWords == 3 ? 8 : 16> draw[2][kBatchSlots * kSlotSteps];
 };
-template <typename T>
+template <typename T, int RANGE>
 constexpr size_t large_lds(int n, int hb) {
-    return (size_t)2 * mat_entries(n) * sizeof(T2<T>) + (hb ? sizeof(LargeRing<T>) : sizeof(LargeRing<T>::a));
+    using Ring = LargeRing<T, RANGE>;
+    return (size_t)2 * mat_entries(n) * sizeof(T2<T>) + (hb ? sizeof(Ring) : sizeof(Ring::a));
 }
 
 static __constant__ pairs::Table<kSlotSteps> kSlotTable = pairs::make_table<kSlotSteps>();
@@ -347,7 +360,7 @@ __device__ __forceinline__ void update_link_large(T2<T>* __restrict__ U, const G
     const Places<kLoads> pl(n, n2);
     T2<T>* const B0 = reinterpret_cast<T2<T>*>(smem_large);
     T2<T>* const B1 = B0 + mat_entries(n);
-    LargeRing<T>& ring = *reinterpret_cast<LargeRing<T>*>(B1 + mat_entries(n));
+    LargeRing<T, RANGE>& ring = *reinterpret_cast<LargeRing<T, RANGE>*>(B1 + mat_entries(n));
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kLanes);  // wavefront
     const int Vh = g.Vh;
     const Site x = site_of(g, par, h);

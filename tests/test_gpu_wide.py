@@ -424,6 +424,14 @@ def test_wide_heatbath_in_the_creutz_range(gpu, nc, dtype, scale):
                   decisions=(np.prod(L) // 2) * nc * (nc - 1) // 2)
 
 
+@pytest.mark.parametrize("nc", [25, 26, 32])
+@pytest.mark.parametrize("scale", [0.02, 0.3])
+def test_wide_heatbath_with_three_creutz_words(gpu, nc, scale):
+    """Records whose three attempts serve the Creutz range (FP64, the largest
+    form), on both sides of its odd and even Nc."""
+    test_wide_heatbath_in_the_creutz_range(gpu, nc, "f64", scale)
+
+
 @pytest.mark.parametrize("nc,dtype,L", [(5, "f32", (6, 2, 1, 2)), (6, "f64", (2, 2, 2, 2)), (7, "f32", (4, 2, 2, 2)),
                                         (8, "f64", (6, 2, 1, 1)), (12, "f32", (4, 2, 2, 2)), (17, "f64", (2, 2, 2, 2)),
                                         (20, "f32", (2, 2, 2, 2)), (25, "f64", (2, 2, 1, 2)), (31, "f32", (2, 2, 2, 2))])
