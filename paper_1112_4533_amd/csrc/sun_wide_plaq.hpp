@@ -306,11 +306,13 @@ __global__ __launch_bounds__(plaq_threads(FORM)) void k_plaquette_large(const T2
                                                                          double* __restrict__ partial) {
     plaquette_site_large<T, FORM>(U, g, n, xcd_tile((int)blockIdx.x, (int)gridDim.x), partial);
 }
+// The chains of a batch group that have from .. to - 1 sites.
 template <typename T, int FORM>
 __global__ __launch_bounds__(plaq_threads(FORM)) void k_plaquette_large_batch(const ChainDesc* __restrict__ d,
-                                                                               int nchains, int n) {
+                                                                              int nchains, int n, int from, int to) {
     const int tile = xcd_tile((int)blockIdx.x, (int)gridDim.x);
     const int c = find_chain<TILE_SITE>(d, nchains, tile);
+    if (d[c].g.V < from || d[c].g.V >= to) return;
     plaquette_site_large<T, FORM>((const T2<T>*)d[c].links, d[c].g, n, tile - d[c].tile0[TILE_SITE], d[c].scratch);
 }
 

@@ -465,12 +465,22 @@ def test_wide_reunitarize_row_layouts(gpu, nc, noise):
     assert to_np(lat.unitarity()).max() < 1e-13
 
 
-@pytest.mark.parametrize("nc,dtype,L", [(17, "f32", (2, 2, 2, 2)), (18, "f64", (4, 2, 2, 1)), (19, "f32", (2, 2, 2, 4)),
-                                        (20, "f64", (2, 2, 2, 2)), (21, "f32", (2, 2, 2, 2))])
+@pytest.mark.parametrize("nc,dtype,L", [(17, "f32", (4, 4, 8, 8)), (17, "f64", (4, 4, 8, 8)), (18, "f64", (32, 32, 1, 1)),
+                                        (18, "f32", (16, 8, 1, 8)), (19, "f32", (4, 4, 8, 8)), (20, "f64", (10, 16, 4, 4)),
+                                        (20, "f32", (10, 16, 4, 4)), (19, "f64", (4, 4, 4, 14)), (20, "f32", (4, 2, 2, 2)),
+                                        (21, "f32", (2, 2, 2, 2))])
 def test_wide_plaquette_rows_and_columns_past_a_tile(gpu, nc, dtype, L):
-    """Nc = 17 ... 20: one tile and its rows and columns past 15 (33, 68, 105
-    and 144 entries); the first Nc of the four tiles after them."""
-    test_wide_plaquette_of_every_tile_form(gpu, nc, dtype, L)
+    """Nc = 17 ... 20 from four (Nc = 20: ten) sites per CU on: one tile and its
+    rows and columns past 15 (33, 68, 105 and 144 entries); just below that and
+    at Nc = 21 the four tiles."""
+    lat = gpu_lattice(gpu, nc, L, dtype, hot=True, seed=71)
+    U = to_np(lat.export())
+    np.testing.assert_allclose(to_np(lat.plaquette()), O.plaquette(U, nc, L), rtol=1e-13, atol=1e-15)
+    # the same bits in a batch beside small and large chains
+    others = [gpu_lattice(gpu, nc, E, dtype, hot=True, seed=72) for E in ((2, 2, 2, 2), (8, 8, 8, 6))]
+    bt = gpu.Batch([others[0], lat, others[1]], [1.0] * 3, [1, 2, 3])
+    for got, chain in zip(to_np(bt.plaquette()), (others[0], lat, others[1])):
+        assert np.array_equal(got, to_np(chain.plaquette()))
 
 
 @pytest.mark.parametrize("nc,noise", [(18, 1e-3), (19, 1e-3), (17, 1.0), (18, 1.0)])
