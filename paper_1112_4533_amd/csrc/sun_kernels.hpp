@@ -340,6 +340,21 @@ __device__ __forceinline__ Quat<T> staple_su2(const T2<T>* __restrict__ U, const
     return A;
 }
 
+// |p|^2 with its roundings written out: of the first two squares one is rounded
+// alone and the other fused onto it.  Every form of the update takes the sum
+// from here, so that a link has the same bits in each of them.
+template <typename T>
+__device__ __forceinline__ T norm2(const Quat<T>& p, bool first_alone) {
+    const T s = first_alone ? fmadd(p.q[1], p.q[1], p.q[0] * p.q[0]) : fmadd(p.q[0], p.q[0], p.q[1] * p.q[1]);
+    return fmadd(p.q[3], p.q[3], fmadd(p.q[2], p.q[2], s));
+}
+// Which of the two, for subgroup step sg of the register path: an arbitrary
+// choice, but one that a chain's bits depend on.
+template <int N, typename T, bool HB>
+__host__ __device__ constexpr bool first_alone(int sg) {
+    return HB && sg > 0 && !(N == 4 && sizeof(T) == 8);
+}
+
 // Normalised subgroup direction V = P / |P| (identity when P = 0), k2 = |P|^2;
 // returns k.
 template <typename T>
@@ -362,10 +377,6 @@ __device__ __forceinline__ T unit_quat(const Quat<T>& p, T k2, Quat<T>& v) {
         v = Quat<T>{{T(1), T(0), T(0), T(0)}};
     }
     return k;
-}
-template <typename T>
-__device__ __forceinline__ T unit_quat(const Quat<T>& p, Quat<T>& v) {
-    return unit_quat(p, p.q[0] * p.q[0] + p.q[1] * p.q[1] + p.q[2] * p.q[2] + p.q[3] * p.q[3], v);
 }
 
 // ---------------------------------------------------------------------------
@@ -397,7 +408,8 @@ SUN_MAT_UNROLL
 SUN_MAT_UNROLL
         for (int j = i + 1; j < N; ++j, ++sg) {
             Quat<T> v;
-            const T k = unit_quat(block_quat(W, i, j), v);
+            const Quat<T> p = block_quat(W, i, j);
+            const T k = unit_quat(p, norm2(p, first_alone<N, T, HB>(sg)), v);
             Quat<T> a;
             if (HB) {
                 const T alpha = cb * k;
@@ -426,7 +438,8 @@ __device__ __forceinline__ void update_link_su2(T2<T>* __restrict__ U, const Geo
     const Quat<T> A = staple_su2<T, MU>(U, g, x, par, h);
     const Quat<T> u = NT ? load_quat_stream<T>(U, MU, par, h, g.Vh) : load_quat<T>(U, MU, par, h, g.Vh);
     Quat<T> v;
-    const T k = unit_quat(qmul(u, A), v);
+    const Quat<T> p = qmul(u, A);
+    const T k = unit_quat(p, norm2(p, first_alone<2, T, HB>(0)), v);
     Quat<T> a;
     if (HB) {
         Quat<T> xs;

@@ -264,16 +264,6 @@ __device__ __forceinline__ void add_dir(Vec<N, T>& A, Nbrs<N, T>& n, int r) {
     }
 }
 
-// |p|^2 with the roundings that the compiler gives the one-lane form's own sum:
-// of the first two squares, one is rounded alone and the other fused, and
-// which one depends on where the step stands (equal bits over all steps, types
-// and directions).
-template <bool FIRST0, typename T>
-__device__ __forceinline__ T norm2(const Quat<T>& p) {
-    const T s = FIRST0 ? fmadd(p.q[1], p.q[1], p.q[0] * p.q[0]) : fmadd(p.q[0], p.q[0], p.q[1] * p.q[1]);
-    return fmadd(p.q[3], p.q[3], fmadd(p.q[2], p.q[2], s));
-}
-
 // The heatbath draw of the quad's step (alpha the same on its lanes): 0 when
 // every attempt was rejected, else its number, with the element in x.
 template <typename T>
@@ -368,8 +358,7 @@ __device__ __forceinline__ void steps(Vec<N, T>& U, Vec<N, T>& W, T cb, uint32_t
     p.q[3] = T(0.5) * (from<I>(W.im[I]) - from<J>(W.im[J]));
     p.q[2] = T(0.5) * (from<J>(W.re[I]) - from<I>(W.re[J]));
     p.q[1] = T(0.5) * (from<J>(W.im[I]) + from<I>(W.im[J]));
-    constexpr bool kFirst0 = HB && SG > 0 && !(N == 4 && sizeof(T) == 8);
-    const T k = unit_quat(p, norm2<kFirst0>(p), v);
+    const T k = unit_quat(p, norm2(p, first_alone<N, T, HB>(SG)), v);
     bool apply = true;
     if constexpr (HB) {
         Quat<T> xs;
@@ -493,7 +482,7 @@ __device__ __forceinline__ void update_link_su2(T2<T>* __restrict__ Up, const Ge
     add(std::integral_constant<int, 2>{}, D2);
     Quat<T> v, el;
     const Quat<T> p = qmul(u, A);
-    const T k = unit_quat(p, norm2<false>(p), v);
+    const T k = unit_quat(p, norm2(p, first_alone<2, T, HB>(0)), v);
     bool apply = true;
     if constexpr (HB) {
         Quat<T> xs;

@@ -281,7 +281,7 @@ __device__ __forceinline__ T chain_unit_quat(const Quat<T>& p, Quat<T>& v) {
             return k2 * r;
         }
     }
-    return unit_quat(p, v);
+    return unit_quat(p, p.q[0] * p.q[0] + p.q[1] * p.q[1] + p.q[2] * p.q[2] + p.q[3] * p.q[3], v);
 }
 
 // ---------------------------------------------------------------------------
