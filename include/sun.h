@@ -269,8 +269,8 @@ int sun_sample_su2(int dtype, const double *dev_alpha, int n, uint64_t seed, uin
  * phase).  A batch groups n lattices of any Nc, precision and extents; each
  * chain has its own coupling beta[i] and seed[i].  One launch per phase and
  * per (Nc, storage) group covers every chain of the group (register path:
- * one group per dtype; workgroup-per-link path: one per precision, a
- * workgroup per link of every chain in the group); the chains'
+ * one group per dtype; workgroup-per-link path: one per Nc and
+ * precision); the chains'
  * RNG step counters live in the device table, so a captured graph replays
  * with fresh random numbers.  A chain run in a batch gives bitwise the same
  * field as the same chain run alone with sun_sweep.

@@ -1,5 +1,6 @@
-// ops_wide.hip -- launchers of the large-Nc kernels (one workgroup per link;
-// Nc is a run-time argument, the LDS size follows it).
+// ops_wide.hip -- the large-Nc table of launchers: the kernels of sun_wide.hpp
+// (one wavefront per link or spatial site, Nc a run-time argument, the LDS size
+// following it) are launched here, the others in their own units.
 #include "sun_ops.hpp"
 #include "sun_wide.hpp"
 

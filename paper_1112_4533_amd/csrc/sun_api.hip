@@ -475,7 +475,7 @@ struct sun_batch_s {
         int first, count;      // range of the device table
         int tiles[5];          // total tiles per grid kind (see TileKind)
         int nc;
-        bool wide;             // workgroup-per-link path: tiles count links / sites, one workgroup each
+        bool wide;             // workgroup-per-link path: tiles as wide_*_tiles count them
         // per update kind: default_shape's workgroup; a batch's chains are
         // small and mostly cache-resident, so no wave cap (64 chains: 1.10e10 ->
         // 1.13e10 link updates/s against a 12-wave overrelaxation cap)

@@ -194,7 +194,7 @@ struct Ops {
     void (*import_field)(const Ctx&, const double* in);
     // batches: d is a device table of n chains of this Nc (nc) and storage
     // type; tiles is the total tile count of the grid kind the call uses (on
-    // the workgroup-per-link path: links, sites or links, one workgroup each)
+    // the workgroup-per-link path: wide_*_tiles)
     void (*update_batch)(const ChainDesc* d, int n, int tiles, int kind, int mu, int par, uint32_t step_offset,
                          const Shape& shape, int nc, hipStream_t s);
     void (*reunit_batch)(const ChainDesc* d, int n, int tiles, int nc, hipStream_t s);
@@ -213,7 +213,7 @@ const Ops* ops_nc2(int f64);
 const Ops* ops_nc3(int f64);
 const Ops* ops_nc4(int f64);
 const Ops* ops_nc3_two_row(int f64);  // SU(3), rows 0 and 1 stored
-const Ops* ops_wide(int f64);         // 4 <= Nc <= 32: one workgroup per link, link-major storage
+const Ops* ops_wide(int f64);         // 4 <= Nc <= 32: link-major storage
 
 // Phases of small lattices take four lanes to a link, kQuadLinks links to a
 // wavefront (sun_quad.hpp).  They win while a phase is about one wavefront per

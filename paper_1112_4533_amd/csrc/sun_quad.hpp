@@ -60,7 +60,7 @@ template <int SRC, typename V>
 __device__ __forceinline__ V from(V v) {
     return perm<SRC, SRC, SRC, SRC>(v);
 }
-// v of lane src (a value below 3, the same in the quad)
+// v of lane src of the quad (the same src on its four lanes)
 template <typename V>
 __device__ __forceinline__ V from_first(V v, int src) {
     const V a = from<0>(v), b = from<1>(v), c = from<2>(v), d = from<3>(v);

@@ -1,8 +1,9 @@
-// sun_wide.hpp -- SU(Nc) for large Nc (4 <= Nc <= 32), one workgroup per link
-// (paper Sec. 3, generic SU(Nc) code; Sec. 4, the large-Nc runs at 8^4): the
-// SU(2) draw of the subgroup steps, re-unitarization, observables, start
-// configuration and field transfer.  The phase update is in
-// sun_wide_small.hpp (Nc <= 8) and sun_wide_large.hpp.
+// sun_wide.hpp -- SU(Nc) for large Nc (4 <= Nc <= 32; paper Sec. 3, generic
+// SU(Nc) code; Sec. 4, the large-Nc runs at 8^4): the SU(2) draw of the
+// subgroup steps, start configuration, Polyakov loop and field transfer.  The
+// phase update is in sun_wide_small.hpp (Nc <= 8, four links to a wavefront)
+// and sun_wide_large.hpp (two wavefronts to a link), the plaquette in
+// sun_wide_plaq.hpp, the re-unitarization in sun_wide_reunit.hpp.
 //
 // At large Nc a link no longer fits in one work-item's registers (Nc = 32 is
 // 2048 reals): its matrices live in LDS, spread over the lanes.  Links are
@@ -77,11 +78,10 @@ __device__ __forceinline__ void lds_load(T2<D>* dst, const T2<S>* src, int n) {
     }
 }
 
-// C = A B, or C += A B (n <= 32; C distinct from B, and from A unless acc is
-// false: then C may be A itself, because a lane reads its block of rows
-// completely in the k loop before it stores any of it, the lanes of a row
-// group run that loop together in the one wavefront of the workgroup, and no
-// other lane touches those rows).  With g = 64 / n
+// C = A B (n <= 32; C distinct from B; it may be A itself, because a lane reads
+// its block of rows completely in the k loop before it stores any of it, the
+// lanes of a row group run that loop together in the one wavefront of the
+// workgroup, and no other lane touches those rows).  With g = 64 / n
 // row groups, lane l < g n owns column j = l mod n and rows i0, i0 + g, ...
 // (i0 = l / n), which it takes R at a time: each B_kj it reads serves R rows,
 // and the n lanes of a row group read the same A_ik (an LDS broadcast).  A
@@ -90,8 +90,8 @@ __device__ __forceinline__ void lds_load(T2<D>* dst, const T2<S>* src, int n) {
 // sum over k = 0 .. n-1 in increasing k, with the same complex multiply-add
 // as the plain triple loop.
 template <typename T, int R>
-__device__ __forceinline__ void lds_mm_rows(T2<T>* C, const T2<T>* A, const T2<T>* B, int n, bool acc, int g, int j,
-                                            int i0, int cnt) {
+__device__ __forceinline__ void lds_mm_rows(T2<T>* C, const T2<T>* A, const T2<T>* B, int n, int g, int j, int i0,
+                                            int cnt) {
     for (int t0 = 0; t0 < cnt; t0 += R) {
         int row[R];
         T r[R], m[R];
@@ -101,11 +101,6 @@ __device__ __forceinline__ void lds_mm_rows(T2<T>* C, const T2<T>* A, const T2<T
             row[t] = (i0 + g * tt) * n;
             r[t] = T(0);
             m[t] = T(0);
-            if (acc) {
-                const T2<T> c = C[row[t] + j];
-                r[t] = c.x;
-                m[t] = c.y;
-            }
         }
         // four k per pass, their LDS reads issued together
         int k = 0;
@@ -139,18 +134,18 @@ __device__ __forceinline__ void lds_mm_rows(T2<T>* C, const T2<T>* A, const T2<T
 // The product by one wavefront: 64 / n groups of n lanes, group i0 = lane / n
 // taking column j = lane mod n and rows i0, i0 + g, ... (g groups in all).
 template <typename T>
-__device__ __forceinline__ void lds_mm(T2<T>* C, const T2<T>* A, const T2<T>* B, int n, bool acc) {
+__device__ __forceinline__ void lds_mm(T2<T>* C, const T2<T>* A, const T2<T>* B, int n) {
     const int g = kLanes / n, l = (int)threadIdx.x;
     if (l >= g * n) return;
     const int j = l % n, i0 = l / n;
     const int cnt = (n - i0 + g - 1) / g;  // rows i0 + g t < n of this lane
     const int most = (n + g - 1) / g;      // rows of group 0, the most of any group
     if (most >= 4)
-        lds_mm_rows<T, 4>(C, A, B, n, acc, g, j, i0, cnt);
+        lds_mm_rows<T, 4>(C, A, B, n, g, j, i0, cnt);
     else if (most >= 2)
-        lds_mm_rows<T, 2>(C, A, B, n, acc, g, j, i0, cnt);
+        lds_mm_rows<T, 2>(C, A, B, n, g, j, i0, cnt);
     else
-        lds_mm_rows<T, 1>(C, A, B, n, acc, g, j, i0, cnt);
+        lds_mm_rows<T, 1>(C, A, B, n, g, j, i0, cnt);
 }
 
 // Change of the site index by one step along direction m (periodic), and the
@@ -213,24 +208,13 @@ __device__ __forceinline__ double wave_max(double v) {
     return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
 }
 
-// Every kernel here runs one wavefront per workgroup, and a wavefront's LDS
-// operations complete in the order it issues them: a read issued after a
-// write sees it, whichever lane wrote, and a write issued after a read leaves
-// that read's value alone.  Steps that hand LDS data between lanes therefore
-// need only compiler ordering (a wavefront-scope fence), not a wait for the
-// LDS round trip that a workgroup barrier implies.
+// Orders LDS hand-offs between the lanes of one wavefront: its LDS operations
+// complete in the order it issues them -- a read issued after a write sees it,
+// whichever lane wrote, and a write issued after a read leaves that read's
+// value alone -- so they need only compiler ordering (a wavefront-scope fence),
+// not a wait for the LDS round trip that a workgroup barrier implies.
+// Hand-offs between wavefronts need the barrier.
 __device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
-
-// v on lane `lane` (uniform across the wave), read with readlane.
-__device__ __forceinline__ float lane_value(float v, int lane) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-}
-__device__ __forceinline__ double lane_value(double v, int lane) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(u & 0xffffffffu), lane);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(u >> 32), lane);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
 
 // The scalar steps of the subgroup chain -- the block's norm and its
 // inverse, 1 / alpha, the draw's square roots -- are computed by the lanes
@@ -716,7 +700,7 @@ __global__ __launch_bounds__(kLanes) void k_polyakov(const T2<T>* __restrict__ U
         st.s = s;
         lds_load<double, T>(X, link_at<T>(U, n2, 3, parity_of(st), s >> 1, g.Vh), n);
         __syncthreads();
-        lds_mm<double>(Tm, P, X, n, false);
+        lds_mm<double>(Tm, P, X, n);
         __syncthreads();
         double2* tmp = P;
         P = Tm;
