@@ -353,8 +353,8 @@ def run_batch(steps, sweeps=200, cut=100, tune=True):
         tuned["layout_ms_per_hb_or_step"] = t_layout
     bt = sun.Batch(lats, betas, seeds)
     if tune:
-        best, _ = autotune.tune_batch(bt, reps=2, use_cache=False)
-        tuned["shapes"] = {"heatbath": list(best[0]), "overrelax": list(best[1])}
+        autotune.tune_batch(bt, reps=2, use_cache=False)
+        tuned["shapes"] = {"heatbath": bt.launch[0] or "default", "overrelax": bt.launch[1] or "default"}
     plaq32 = torch.zeros((len(spec), 3), dtype=torch.float64, device="cuda")
     series32 = torch.zeros((sweeps, len(spec)), dtype=torch.float64, device="cuda")
     bt.capture(n_sweeps=1, n_hb=n_hb, n_or=n_or, reunit=True, plaq_out=plaq32)

@@ -7,12 +7,15 @@ t-blocked tile walk of 2, 4 or 8 time slices, and with 1, 2 or 4 sites per
 work-item (searched after the rest, with the chosen shape in place).  Every shape computes the same bits, so the
 choice is a pure speed question, made separately for the heatbath and the
 overrelaxation kernels (the heatbath draws cost arithmetic, so it prefers
-more resident waves).  It depends on the lattice: a small lattice needs small
+more resident waves).  It depends on the lattice: a medium lattice needs small
 workgroups to occupy 256 CUs, a large one the XCD-aware order and a wave cap
-for L2 reuse.  The tuner times heatbath-only and overrelaxation-only steps on
+for L2 reuse.  (The phases of small lattices and of Nc >= 5 have a shape of
+their own: for them the choice changes nothing.)  The tuner times heatbath-only and overrelaxation-only steps on
 a clone of the field (the chain itself is never touched), applies the
 fastest shape of each kind, and remembers the choice in a JSON cache keyed
 by GPU architecture, Nc, extents and storage (or by the chain list of a batch).
+A batch starts with a workgroup per group of chains and kind, which one shape
+for all groups may not match: it keeps that default where none is faster.
 
 For batches the link layout is a dimension too: the FP32 SU(3) chains can be
 stored with all 18 reals or as two rows (12 reals, row 2 rebuilt on load;
@@ -145,13 +148,16 @@ def batch_key(batch):
 
 def tune_batch(batch, reps=3, use_cache=True):
     """As tune_lattice for a batch (timed on a clone of its chains); drops
-    the batch's captured graph."""
+    the batch's captured graph.  The returned shapes are the fastest that all
+    groups can share; a kind for which the batch's default is faster than its
+    one keeps the default (batch.launch[kind] stays None)."""
     key = batch_key(batch)
     cache = _load_cache() if use_cache else {}
     if key in cache:
         best = {int(k): tuple(v) for k, v in cache[key]["shape"].items()}
         for kind, shape in best.items():
-            batch.set_launch(*shape, kind=kind)
+            if batch.launch[kind] is not None or kind not in cache[key].get("default", []):
+                batch.set_launch(*shape, kind=kind)
         for kind, spt in cache[key].get("sites_per_item", {}).items():
             batch.set_sites_per_item(spt, kind=int(kind))
         return best, cache[key].get("ms", {})
@@ -161,17 +167,25 @@ def tune_batch(batch, reps=3, use_cache=True):
         c.links.copy_(l.links)
         clones.append(c)
     cb = sun.Batch(clones, batch.betas, batch.seeds)
+    steps = {sun.HEATBATH: lambda: cb.sweep(1, 0, reunit=False), sun.OVERRELAX: lambda: cb.sweep(0, 1, reunit=False)}
+    names = {sun.HEATBATH: "heatbath", sun.OVERRELAX: "overrelax"}
+    default = {kind: _time(step, reps) for kind, step in steps.items()}
     best, times = _search(sun.Batch.LAUNCH_SHAPES, lambda shape, kind: cb.set_launch(*shape, kind=kind),
-                          lambda: cb.sweep(1, 0, reunit=False), lambda: cb.sweep(0, 1, reunit=False), reps)
+                          steps[sun.HEATBATH], steps[sun.OVERRELAX], reps)
+    times["default"] = {names[kind]: t for kind, t in default.items()}
+    kept = [kind for kind in best if batch.launch[kind] is None
+            and default[kind] <= min(times[names[kind]].values())]
+    cb = sun.Batch(clones, batch.betas, batch.seeds)  # with the default of both kinds
     for kind, shape in best.items():
-        cb.set_launch(*shape, kind=kind)
-        batch.set_launch(*shape, kind=kind)
+        if kind not in kept:
+            cb.set_launch(*shape, kind=kind)
+            batch.set_launch(*shape, kind=kind)
     spt, t_spt = _search_spt(lambda v, kind: cb.set_sites_per_item(v, kind=kind),
-                             lambda: cb.sweep(1, 0, reunit=False), lambda: cb.sweep(0, 1, reunit=False), reps)
+                             steps[sun.HEATBATH], steps[sun.OVERRELAX], reps)
     times.update(t_spt)
     for kind, v in spt.items():
         batch.set_sites_per_item(v, kind=kind)
-    cache[key] = {"shape": {str(k): list(v) for k, v in best.items()},
+    cache[key] = {"shape": {str(k): list(v) for k, v in best.items()}, "default": kept,
                   "sites_per_item": {str(k): v for k, v in spt.items()}, "ms": times}
     if use_cache:
         _save_cache(cache)

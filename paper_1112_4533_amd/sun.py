@@ -341,7 +341,9 @@ class Batch:
         self.n = n
         self.betas = [float(x) for x in betas]
         self.seeds = [int(x) for x in seeds]
-        self.launch = [(256, 1, 0), (256, 1, 0)]    # heatbath, overrelaxation (block, xcd, waves)
+        # heatbath, overrelaxation: (block, xcd, waves) as set, None until then
+        # (each group of chains then has the library's default for its size)
+        self.launch = [None, None]
         self.sites_per_item = [1, 1]
         self.stream = torch.cuda.Stream(device=dev)   # graphs need a non-null stream
 

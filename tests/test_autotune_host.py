@@ -100,3 +100,63 @@ def test_cache_save_is_atomic_and_readable(monkeypatch, tmp_path):
     assert autotune._load_cache() == {"k": {"shape": {"0": [64, 1, 0, 0]}}}
     assert not (tmp_path / "sub" / "tune.json.tmp").exists()
 
+
+
+class FakeChain:
+    nc, L, dtype = 3, (8, 8, 8, 8), 0
+
+    def __init__(self, *args, **kw):
+        self.links = self
+
+    def copy_(self, other):
+        pass
+
+    device = "none"
+
+
+class FakeBatch:
+    """A batch whose steps cost what `cost` says for the shape in force."""
+    LAUNCH_SHAPES = sun.Batch.LAUNCH_SHAPES
+    cost = staticmethod(lambda kind, shape: 1.0)
+    clock = 0.0
+
+    def __init__(self, lattices, betas, seeds):
+        self.lattices, self.betas, self.seeds = lattices, betas, seeds
+        self.launch, self.spt = [None, None], {}
+
+    def set_launch(self, block, xcd, waves, kind=-1):
+        self.launch[kind] = (block, xcd, waves)
+
+    def set_sites_per_item(self, spt, kind=-1):
+        self.spt[kind] = spt
+
+    def sweep(self, n_hb, n_or, reunit=True):
+        FakeBatch.clock = FakeBatch.cost(0 if n_hb else 1, self.launch[0 if n_hb else 1])
+
+
+def test_batch_tuner_keeps_a_faster_default(monkeypatch, tmp_path):
+    """The mixed default of a batch is a candidate: it stays in force for the
+    kind for which no shared shape is faster, also from the cache, and a shape
+    that was set before is never taken for the default."""
+    monkeypatch.setattr(autotune, "_arch", lambda: "gfx950")
+    monkeypatch.setattr(autotune, "CACHE", str(tmp_path / "tune.json"))
+    monkeypatch.setattr(sun, "Batch", FakeBatch)
+    monkeypatch.setattr(sun, "Lattice", type("L", (FakeChain,), {"SITES_PER_ITEM": sun.Lattice.SITES_PER_ITEM}))
+
+    def timed(fn, reps):
+        fn()
+        return FakeBatch.clock
+    monkeypatch.setattr(autotune, "_time", timed)
+    fast = (128, 1, 12)
+    # heatbath: the default is fastest; overrelaxation: one shared shape is
+    monkeypatch.setattr(FakeBatch, "cost", staticmethod(
+        lambda kind, shape: (0.5 if kind == 0 else 2.0) if shape is None else 1.0 if shape == fast else 1.5))
+    first, cached, was_set = (FakeBatch([FakeChain()], [6.0], [1]) for _ in range(3))
+    best, times = autotune.tune_batch(first)
+    assert best == {0: fast, 1: fast} and first.launch == [None, fast]
+    assert times["default"] == {"heatbath": 0.5, "overrelax": 2.0}
+    assert set(first.spt) == {0, 1}
+    assert autotune.tune_batch(cached)[0] == best and cached.launch == [None, fast]
+    was_set.set_launch(256, 1, 0, kind=0)
+    autotune.tune_batch(was_set)
+    assert was_set.launch == [fast, fast]
