@@ -666,19 +666,20 @@ int sun_batch_create(int n, const sun_lattice_t* chains, const double* betas, co
         }
         if (!gr.count) continue;
         if (!gr.wide) {
-            // all the group's links, and those of chains that have all four
-            // directions or large planes: the group goes by most of them
-            long long links = 0, full = 0, far = 0;
+            // all the group's links, and those of chains that have at least three
+            // directions, four, or large planes: the group goes by most of them
+            long long links = 0, three = 0, four = 0, far = 0;
             for (int i = gr.first; i < gr.first + gr.count; ++i) {
                 const sun::PhaseGrid p = sun::phase_grid(b->host[i].g, true);
                 links += p.links;
-                if (p.full) full += p.links;
+                if (p.dirs >= 3) three += p.links;
+                if (p.dirs == 4) four += p.links;
                 if (p.far) far += p.links;
             }
             const sun_lattice_t h = chains[b->host[gr.first].out_index];
             for (int k = 0; k < 2; ++k) {
-                const sun::Shape sh = sun::default_shape(nc, is_f64(dt), h->link_bytes / (4 * (size_t)h->g.V),
-                                                         sun::PhaseGrid{links, 2 * full > links, 2 * far > links},
+                const sun::PhaseGrid grid{links, 2 * four > links ? 4 : 2 * three > links ? 3 : 2, 2 * far > links};
+                const sun::Shape sh = sun::default_shape(nc, is_f64(dt), h->link_bytes / (4 * (size_t)h->g.V), grid,
                                                          k == SUN_HEATBATH);
                 gr.shape[k].block = sh.block;
                 gr.shape[k].ahead = sh.ahead;

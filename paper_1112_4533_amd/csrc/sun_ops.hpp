@@ -113,12 +113,12 @@ inline bool valid_phase_block(int b) { return b == 64 || b == 128 || b == 256; }
 // What a phase's default launch shape follows from besides the link type.
 struct PhaseGrid {
     long long links;  // links a phase updates
-    bool full;        // all four directions present
+    int dirs;         // directions present
     bool far;         // 64-item workgroups would walk linearly over large planes
 };
 inline PhaseGrid phase_grid(const Geom& g, bool linear) {  // linear: the walk is never t-blocked (a batch's)
     const int plane = g.L[0] * g.L[1] / 2;
-    return PhaseGrid{g.Vh, g.present == 15, plane > 12 * 64 && (linear || plane % 64 != 0 || g.L[3] % 4 != 0)};
+    return PhaseGrid{g.Vh, __builtin_popcount(g.present), plane > 12 * 64 && (linear || plane % 64 != 0 || g.L[3] % 4 != 0)};
 }
 
 // Workgroup, wave cap and walk that a phase starts with; a tuner or the caller
@@ -153,9 +153,11 @@ inline PhaseGrid phase_grid(const Geom& g, bool linear) {  // linear: the walk i
 //     walks linearly over planes of more than twelve wavefronts (40^4 445 -> 458,
 //     44^4 696 -> 702; 36^4, of ten, 263 -> 261; 48^4, t-blocked, 936 -> 789); the
 //     heatbath not (20^4 36.3 -> 38.3)
-//   SU(3) with a direction absent: never.  The loads ahead are issued for it
-//     too, and a wavefront of fewer staples does better with others beside it
-//     (256 512 FP32 7.6/12.8 -> 10.7/16.1, 48^3 9.4/12.6 -> 10.8/14.4; FP64
+//   SU(3) with a direction absent: only in three, up to half a wavefront per SIMD
+//     (40^3 FP32 8.8/11.6 -> 8.3/11.0, FP64 32 32 64 9.6/19.6 -> 9.2/18.9).  The loads
+//     ahead are issued for the absent direction too, and a wavefront of fewer
+//     staples does better with others beside it (48 48 40 FP32 9.1/12.3 -> 9.5/12.9,
+//     48^3 9.4/12.6 -> 10.8/14.4, 256 512 7.6/12.8 -> 10.7/16.1; FP64
 //     overrelaxation 512^2 17.4 -> 22.3, 56^3 19.5 -> 21.7).
 // Wave caps of larger grids, from sweeps on SU(3) 32^4: the heatbath 16
 // resident waves per CU whatever the storage, the overrelaxation 12 for
@@ -165,13 +167,13 @@ inline PhaseGrid phase_grid(const Geom& g, bool linear) {  // linear: the walk i
 inline Shape default_shape(int nc, bool f64, size_t link_bytes, const PhaseGrid& grid, bool heatbath) {
     const long long per_simd = 1024 * 64;  // links of one wavefront on every SIMD
     const long long few = nc != 3 ? 2 * per_simd : !f64 ? per_simd * 3 / 2 : link_bytes > 96 ? per_simd - 1 : per_simd;
-    if (nc == 3 && !grid.full) return Shape{256, 1, heatbath ? 16 : link_bytes > 48 ? 8 : 12, 4};
-    if (grid.links <= few) {
+    const long long few3 = grid.dirs == 4 ? few : grid.dirs == 3 ? per_simd / 2 : 0;
+    if (grid.links <= (nc == 3 ? few3 : few)) {
         const bool late = !f64 && !heatbath && link_bytes > 48 && grid.links > per_simd * 5 / 4;
         return Shape{64, 1, 0, 0, 1, nc == 3 && !late};
     }
-    if (nc == 3) {
-        if (f64 && !heatbath && !grid.far) return Shape{64, 1, 8, 4, 1, grid.links > per_simd * 3 / 2};
+    if (nc == 3 && grid.dirs == 4) {
+        if (f64 && !heatbath && !grid.far) return Shape{64, 1, 8, 4, 1, grid.links >= per_simd * 3 / 2};
         const bool many = heatbath ? link_bytes > 48 && grid.links >= 4 * per_simd
                                    : grid.links >= (link_bytes > 48 ? 8 : 6) * per_simd;
         if (!f64 && many) return Shape{64, 1, 8, 4, 1, true};

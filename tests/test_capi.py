@@ -149,7 +149,9 @@ def test_create_validates_buffers_without_touching_them(lib):
 
 @pytest.mark.parametrize("nc,L,dtype,hb,orx", [
     # medium and large SU(3) lattices start with 64-item workgroups where all
-    # four directions are present, never with one absent
+    # four directions are present, with one absent only the smallest of them
+    (3, (40, 40, 40, 1), 0, (64, 1, 0, 0), (64, 1, 0, 0)),
+    (3, (48, 48, 40, 1), 0, (256, 1, 16, 0), (256, 1, 8, 0)),
     (3, (16, 16, 16, 16), 0, (64, 1, 0, 0), (64, 1, 0, 0)),
     (3, (32, 32, 32, 32), 1, (256, 1, 16, 4), (64, 1, 8, 4)),
     (3, (256, 512, 1, 1), 0, (256, 1, 16, 0), (256, 1, 8, 0)),

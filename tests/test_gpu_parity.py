@@ -783,7 +783,7 @@ def test_launch_shapes_past_the_small_lattices(gpu, nc, dtype, L):
 @pytest.mark.parametrize("dtype,L", [("f32", (32, 16, 10, 8)), ("f32", (32, 32, 32, 8)), ("f32r12", (32, 32, 32, 8)),
                                       ("f64", (32, 32, 16, 10)), ("f64r12", (32, 32, 16, 14)),
                                       ("f32", (20, 20, 20, 24)),
-                                      ("f32", (64, 32, 1, 32))])
+                                      ("f32", (64, 32, 1, 32)), ("f64", (64, 32, 34, 1))])
 def test_su3_workgroups_of_64_on_either_side_of_their_lines(gpu, dtype, L):
     """SU(3) shapes of 64 items issue the staple's loads ahead only where they
     are the default (here: the first lattice, and the overrelaxation of
